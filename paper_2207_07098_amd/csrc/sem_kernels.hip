@@ -285,6 +285,31 @@ __device__ __forceinline__ void load_g6(const bf16_t *plane, int col, float (&g)
     unpack_g6(plane, load_g6_raw(plane, col), g);
 }
 
+// The factors of one point between their request and their use: six values,
+// or for 16-bit factors the 12 bytes as loaded (widening them at the load
+// would wait for it there).
+template <typename GS>
+struct Fac {
+    typename GT<GS>::T v[6];
+    template <int C>
+    __device__ __forceinline__ void load(const GS *plane, int col) { load_g6<C>(plane, col, v); }
+    __device__ __forceinline__ void get(typename GT<GS>::T (&g)[6]) const {
+#pragma unroll
+        for (int a = 0; a < 6; ++a) g[a] = v[a];
+    }
+};
+template <typename GS>
+struct Fac16 {
+    u3v w;
+    template <int C>
+    __device__ __forceinline__ void load(const GS *plane, int col) { w = load_g6_raw(plane, col); }
+    __device__ __forceinline__ void get(float (&g)[6]) const { unpack_g6((const GS *)nullptr, w, g); }
+};
+template <>
+struct Fac<_Float16> : Fac16<_Float16> {};
+template <>
+struct Fac<bf16_t> : Fac16<bf16_t> {};
+
 // Waves per SIMD the compiler must allow for: bounds the register budget.
 template <int N1, typename GS, int PF = N1>
 struct AxOcc {
@@ -300,6 +325,13 @@ struct AxOcc {
     static constexpr int value = (sizeof(GS) == 2 && N1 == 8) ? 4
                                  : (PF >= N1 ? all_planes : ring);
 };
+
+// A finished or paused CG skips the operator (both flags in one round trip).
+__device__ __forceinline__ bool cg_stopped(const CgState *st) {
+    if (!st) return false;
+    const int done = st->done, pause = st->pause;
+    return (done | pause) != 0;
+}
 
 // Per-workgroup geometry of the element loop: lane -> (slot, column i,j).
 template <int N1>
@@ -339,12 +371,15 @@ struct AxMesh {
 template <int N1>
 __device__ __forceinline__ void load_map(const int32_t *bmap, const Lane<N1> &L, int64_t e,
                                          int32_t (&bm)[N1]) {
-    constexpr int N = N1 - 1, NP = N1 * N1 * N1, NB = NP - (N - 1) * (N - 1) * (N - 1);
+    constexpr int N = N1 - 1, C1 = N1 * N1, NP = C1 * N1, NB = NP - (N - 1) * (N - 1) * (N - 1);
+    const int32_t *be = bmap + e * NB;
 #pragma unroll
     // streamed once per application: non-temporal, so that it does not evict
-    // the u and y lines that neighbouring elements reuse
+    // the u and y lines that neighbouring elements reuse.  Interior lanes
+    // read the first entry of the plane's ring and never use it: a load under
+    // a divergent branch would cost a branch and a wait of its own
     for (int k = 0; k < N1; ++k)
-        bm[k] = L.bpt(k) ? __builtin_nontemporal_load(bmap + e * NB + L.bpos(k)) : -1;
+        bm[k] = __builtin_nontemporal_load(be + (L.bpt(k) ? L.bpos(k) : C1 + (k - 1) * 4 * N));
 }
 
 // u_e = (Q M u)_e for one lane's column of element e: one unconditional load
@@ -402,13 +437,35 @@ enum { MODE_ATOMIC = 0, MODE_COMPACT = 1, MODE_LOCAL = 2 };
 // HELM: the Helmholtz operator h1 D^T G D + h2 B of the velocity solve
 // (Sec. II-A, last paragraph): the element's mass values are streamed with
 // its factors, u is read back from LDS at the output.
-template <int N1, typename GS, int MODE, typename VT = typename GT<GS>::T, int PF = N1,
-          bool HELM = false>
+// EARLY: the workgroup has one element group, and the caller has requested
+// the first planes of its factors already, together with the map entries and
+// before the gather, so the wave sees two memory round trips instead of
+// three.  It pays for 32- and 16-bit factors, whose launches are bound by
+// that chain (48^3, N = 7: FP32 0.335 -> 0.328 ms, FP16 0.318 -> 0.302 ms;
+// 24^3: 0.0545 -> 0.0518 and 0.0561 -> 0.0526 ms).  FP64 launches are bound
+// by HBM, and factors ahead of the gather only delay it (24^3: 0.086 -> 0.091
+// ms).  In the loop over groups the gather goes first as well: there the map
+// comes from the previous element, and factor registers that live across
+// elements spill.
+template <int N1, int PF>
+constexpr int kFacRegs = PF >= N1 ? N1 : PF + 1;
+
+template <int N1, typename GS, int PF>
+__device__ __forceinline__ void load_factors(const GS *G, int64_t ec, int col,
+                                             Fac<GS> (&g)[kFacRegs<N1, PF>]) {
+    constexpr int C = N1 * N1;
+    const GS *Ge = G + (size_t)ec * C * N1 * 6;
+#pragma unroll
+    for (int k = 0; k < (PF >= N1 ? N1 : PF); ++k) g[k].template load<C>(Ge + (size_t)k * C * 6, col);
+}
+
+template <int N1, typename GS, int MODE, typename VT, int PF, bool HELM, bool EARLY>
 __device__ __forceinline__ void ax_element(const AxMesh<GS> &M, const typename GT<GS>::T *Dg,
                                            const typename GT<GS>::T *DTg,
                                            const typename GT<GS>::T *Dl, const Lane<N1> &L,
                                            typename GT<GS>::T *S0, int64_t ec, bool active,
-                                           int64_t next_e, int32_t (&bm)[N1], bool want_dot,
+                                           int64_t next_e, int32_t (&bm)[N1],
+                                           Fac<GS> (&g)[kFacRegs<N1, PF>], bool want_dot,
                                            double &dot) {
     using T = typename GT<GS>::T;
     Dg = uniform_ptr(Dg);
@@ -430,8 +487,7 @@ __device__ __forceinline__ void ax_element(const AxMesh<GS> &M, const typename G
     VT *__restrict__ WB = reinterpret_cast<VT *>(M.wb);
 
     constexpr bool ALL = PF >= N1;
-    constexpr int NS = ALL ? N1 : PF + 1;
-    T g[NS][6];
+    constexpr int NS = kFacRegs<N1, PF>;
     const GS *Ge = M.G + (size_t)ec * NP * 6;
     // ---- gather u_e = (Q M u)_e first: memory counters retire in issue
     // order, so the derivatives can start while the factors still arrive
@@ -462,8 +518,7 @@ __device__ __forceinline__ void ax_element(const AxMesh<GS> &M, const typename G
         }
     }
     // ---- then the factors of the first planes (all of them, or the ring)
-#pragma unroll
-    for (int k = 0; k < (ALL ? N1 : PF); ++k) load_g6<C>(Ge + (size_t)k * C * 6, col, g[k % NS]);
+    if (!EARLY) load_factors<N1, GS, PF>(M.G, ec, col, g);
     double bl[HELM ? N1 : 1];
     if constexpr (HELM) {
 #pragma unroll
@@ -471,7 +526,7 @@ __device__ __forceinline__ void ax_element(const AxMesh<GS> &M, const typename G
             bl[k] = __builtin_nontemporal_load(M.B + (size_t)ec * NP + k * C + col);
     }
     // ---- map entries of the next element
-    if (!IN_LOCAL && next_e >= 0) load_map<N1>(M.bmap, L, next_e, bm);
+    if (!EARLY && !IN_LOCAL && next_e >= 0) load_map<N1>(M.bmap, L, next_e, bm);
 
 #pragma unroll
     for (int k = 0; k < N1; ++k) S0[k * PLANE + j * PITCH + i] = u[k];
@@ -498,8 +553,9 @@ __device__ __forceinline__ void ax_element(const AxMesh<GS> &M, const typename G
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
         if (!ALL && k + PF < N1)
-            load_g6<C>(Ge + (size_t)(k + PF) * C * 6, col, g[(k + PF) % NS]);
-        const T *gk = g[k % NS];
+            g[(k + PF) % NS].template load<C>(Ge + (size_t)(k + PF) * C * 6, col);
+        T gk[6];
+        g[k % NS].get(gk);
         T ur = 0, us = 0;
         const T ut = wt[k];
 #pragma unroll
@@ -560,34 +616,24 @@ __device__ __forceinline__ void ax_element(const AxMesh<GS> &M, const typename G
     if (HELM && want_dot && active) dot += M.h2 * hdot;
 }
 
-template <int N1, typename T>
-__device__ __forceinline__ void fill_dl(T *Dl, const T *Dg);
-
-template <int N1, typename T>
-__device__ __forceinline__ void fill_dl(T *Dl, const T *Dg) {
-    constexpr int C = N1 * N1;
-    for (int q = threadIdx.x; q < C; q += blockDim.x) Dl[q] = Dg[q];
-}
 
 // Persistent pass over element groups of one mesh.  Per element the factors
 // of all planes and the gathered u are requested together (the element's
 // map entries were fetched while the previous element was computed), so a
 // wave waits about one memory latency per element.
-template <int N1, typename GS, int MODE, typename VT, int PF = N1, bool HELM = false>
+template <int N1, typename GS, int MODE, typename VT, int PF, bool HELM, bool EARLY>
 __global__ void __attribute__((amdgpu_flat_work_group_size(1, 256),
                                amdgpu_waves_per_eu(AxOcc<N1, GS, PF>::value)))
 k_ax(AxParams<N1, GS> P) {
     using T = typename GT<GS>::T;
     constexpr int C = N1 * N1, BUF = N1 * N1 * (N1 + 1);
-    CgState *st = P.st;
-    if (st && (st->done || st->pause)) return;
+    if (cg_stopped(P.st)) return;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     // one LDS slot per element of the group (the workgroup has exactly
     // epb * (N+1)^2 lanes; its last wave may be partial)
     const Lane<N1> L(threadIdx.x);
     T *S0 = reinterpret_cast<T *>(smem_raw) + (size_t)L.slot * 3 * BUF;
     T *Dl = reinterpret_cast<T *>(smem_raw) + (size_t)P.epb * 3 * BUF;
-    fill_dl<N1, T>(Dl, P.D);
     AxMesh<GS> M{P.u, P.y, P.wb, P.G, P.gscale, P.bmap, P.E, P.n_bnd, P.in_local, P.out_mode,
                  P.B, P.h1, P.h2};
     auto elem_of = [&](int64_t git, bool &act) {
@@ -596,20 +642,33 @@ k_ax(AxParams<N1, GS> P) {
         act = (L.slot < P.epb) && (e < P.E);
         return act ? e : (int64_t)0;     // inactive lanes read element 0
     };
+    // map entries, D and (EARLY) factors are requested together, before
+    // anything is waited for
     int32_t bm[N1];
+    Fac<GS> g[kFacRegs<N1, PF>];
     {
         bool act;
         const int64_t e0 = elem_of(blockIdx.x, act);
         if (MODE != MODE_LOCAL) load_map<N1>(P.bmap, L, e0, bm);
+        const T d = threadIdx.x < C ? P.D[threadIdx.x] : T(0);   // at least C lanes
+        if (EARLY) load_factors<N1, GS, PF>(P.G, e0, L.col, g);
+        if (threadIdx.x < C) Dl[threadIdx.x] = d;
     }
     __syncthreads();
     double dot = 0.0;
-    for (int64_t git = blockIdx.x; git < P.ngroups; git += gridDim.x) {
-        bool active, act_n;
-        const int64_t ec = elem_of(git, active);
-        const int64_t en = git + gridDim.x < P.ngroups ? elem_of(git + gridDim.x, act_n) : -1;
-        ax_element<N1, GS, MODE, VT, PF, HELM>(M, P.D, P.DT, Dl, L, S0, ec, active, en, bm,
-                                               P.partials != nullptr, dot);
+    if constexpr (EARLY) {
+        bool active;
+        const int64_t ec = elem_of(blockIdx.x, active);
+        ax_element<N1, GS, MODE, VT, PF, HELM, EARLY>(M, P.D, P.DT, Dl, L, S0, ec, active, -1, bm,
+                                                     g, P.partials != nullptr, dot);
+    } else {
+        for (int64_t git = blockIdx.x; git < P.ngroups; git += gridDim.x) {
+            bool active, act_n;
+            const int64_t ec = elem_of(git, active);
+            const int64_t en = git + gridDim.x < P.ngroups ? elem_of(git + gridDim.x, act_n) : -1;
+            ax_element<N1, GS, MODE, VT, PF, HELM, EARLY>(M, P.D, P.DT, Dl, L, S0, ec, active, en,
+                                                          bm, g, P.partials != nullptr, dot);
+        }
     }
     if (P.partials) {
         double v[1] = {dot};
@@ -712,8 +771,7 @@ __global__ void __launch_bounds__(256) k_ax_mfma(AxParams<8, GS> P) {
     static_assert(NP == kMfmaPart, "one element per MFMA slot");
     using E = typename MF<GS>::E;
     using V = typename MF<GS>::V;
-    CgState *st = P.st;
-    if (st && (st->done || st->pause)) return;
+    if (cg_stopped(P.st)) return;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const Lane<N1> L(threadIdx.x);
     const int lane = threadIdx.x & 63;
@@ -886,33 +944,19 @@ __device__ __forceinline__ void mfma32_dir(const float (&a)[4], const float *src
     }
 }
 
-template <typename GS, typename VT>
+template <typename GS, typename VT, bool EARLY>
 __global__ void __launch_bounds__(256) k_ax_mfma32(AxParams<8, GS> P) {
     // three waves per SIMD (about 160 registers with the MFMA results);
     // capped at four it spills 10 registers and is 10% slower
     constexpr int N1 = 8, N = 7, C = 64, NP = 512;
     static_assert(6 * NP * 4 == kMfmaSlotBytes, "FP32 matrix-core slot layout");
     constexpr bool SCALED = sizeof(GS) == 2;
-    CgState *st = P.st;
-    if (st && (st->done || st->pause)) return;
+    if (cg_stopped(P.st)) return;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const Lane<N1> L(threadIdx.x);
     const int lane = threadIdx.x & 63;
     float *UR = reinterpret_cast<float *>(smem_raw + (size_t)L.slot * kMfmaSlotBytes);
     float *US = UR + NP, *UT = US + NP, *FR = UT + NP, *FS = FR + NP, *FT = FS + NP;
-    // A operands diag(D, D) and diag(D^T, D^T): step s, row lane % 16,
-    // contraction entry 4 s + lane / 16
-    float aF[4], aB[4];
-    {
-        const int row = lane & 15, q = lane >> 4;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int kk = 4 * s + q;
-            const bool blk = (row >> 3) == (kk >> 3);
-            aF[s] = blk ? (float)P.D[(row & 7) * N1 + (kk & 7)] : 0.f;
-            aB[s] = blk ? (float)P.D[(kk & 7) * N1 + (row & 7)] : 0.f;
-        }
-    }
     AxMesh<GS> M{P.u, P.y, P.wb, P.G, P.gscale, P.bmap, P.E, P.n_bnd, 0, OUT_ATOMIC,
                  nullptr, 1.0, 0.0};
     VT *__restrict__ Y = reinterpret_cast<VT *>(P.y);
@@ -922,10 +966,30 @@ __global__ void __launch_bounds__(256) k_ax_mfma32(AxParams<8, GS> P) {
         act = (L.slot < P.epb) && (e < P.E);
         return act ? e : (int64_t)0;           // inactive waves work on element 0
     };
+    // the first element's map entries and factors together (as in k_ax);
+    // 16-bit factors stay packed (3 registers per point) until use
     int32_t bm[N1];
+    Fac<GS> g[N1];
     {
         bool act;
-        load_map<N1>(P.bmap, L, elem_of(blockIdx.x, act), bm);
+        const int64_t e0 = elem_of(blockIdx.x, act);
+        load_map<N1>(P.bmap, L, e0, bm);
+        if (EARLY) load_factors<N1, GS, N1>(P.G, e0, col, g);
+    }
+    // A operands diag(D, D) and diag(D^T, D^T): step s, row lane % 16,
+    // contraction entry 4 s + lane / 16
+    float aF[4], aB[4];
+    {
+        const int row = lane & 15, q = lane >> 4;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int kk = 4 * s + q;
+            const bool blk = (row >> 3) == (kk >> 3);
+            const float f = (float)P.D[(row & 7) * N1 + (kk & 7)];
+            const float b = (float)P.D[(kk & 7) * N1 + (row & 7)];
+            aF[s] = blk ? f : 0.f;
+            aB[s] = blk ? b : 0.f;
+        }
     }
     double dot = 0.0;
     for (int64_t git = blockIdx.x; git < P.ngroups; git += gridDim.x) {
@@ -933,17 +997,10 @@ __global__ void __launch_bounds__(256) k_ax_mfma32(AxParams<8, GS> P) {
         const int64_t ec = elem_of(git, active);
         int32_t bidx[N1];
         float u[N1];
-        // factors: 16-bit ones stay packed (3 registers per point) until use
-        float g[SCALED ? 1 : N1][6];
-        u3v graw[SCALED ? N1 : 1];
         gather_u<N1, GS, VT>(M, L, ec, active, bm, u, bidx);
-        const GS *Ge = P.G + (size_t)ec * NP * 6;
-#pragma unroll
-        for (int k = 0; k < N1; ++k) {
-            if constexpr (SCALED) graw[k] = load_g6_raw(Ge + (size_t)k * C * 6, col);
-            else load_g6<C>(Ge + (size_t)k * C * 6, col, g[k]);
-        }
-        if (git + gridDim.x < P.ngroups) load_map<N1>(P.bmap, L, elem_of(git + gridDim.x, act_n), bm);
+        if (!EARLY) load_factors<N1, GS, N1>(P.G, ec, col, g);
+        if (!EARLY && git + gridDim.x < P.ngroups)
+            load_map<N1>(P.bmap, L, elem_of(git + gridDim.x, act_n), bm);
 #pragma unroll
         for (int k = 0; k < N1; ++k) {
             UR[k * C + j * N1 + i] = u[k];
@@ -969,10 +1026,7 @@ __global__ void __launch_bounds__(256) k_ax_mfma32(AxParams<8, GS> P) {
                 const float us = FS[k * C + i * N1 + j];
                 const float ut = utv[k];
                 float gk[6];
-                if constexpr (SCALED) unpack_g6(Ge, graw[k], gk);
-                else
-#pragma unroll
-                    for (int a = 0; a < 6; ++a) gk[a] = g[k][a];
+                g[k].get(gk);
                 const float wr = gk[0] * ur + gk[3] * us + gk[4] * ut;
                 const float ws = gk[3] * ur + gk[1] * us + gk[5] * ut;
                 wtv[k] = gk[4] * ur + gk[5] * us + gk[2] * ut;
@@ -1007,6 +1061,7 @@ __global__ void __launch_bounds__(256) k_ax_mfma32(AxParams<8, GS> P) {
                 }
             }
         }
+        if (EARLY) break;
         __syncthreads();                        // LDS is rewritten by the next element
     }
     if (P.partials) {
@@ -1063,75 +1118,59 @@ hipError_t ax_dispatch_n(sem_ctx c, const void *Gp, const float *gscale, const v
     if (grid > P.ngroups) grid = P.ngroups;
     if (P.xcd && grid < P.ngroups && (grid & 7)) P.xcd = 0;
     const bool ring = t.pipeline == 1;       // factor planes in flight: 2 instead of all
+    // one element group per workgroup and reduced-precision factors: requested
+    // before the gather (see EARLY)
+    const bool early = sizeof(GS) < 8 && grid == P.ngroups;
+    const dim3 g((unsigned)grid), b(threads);
+    // the E-vector and fixed-order forms take the planes in flight that suit
+    // the order: all of them, in FP64 from N = 9 a ring of two (all planes run
+    // at one wave per SIMD there: 439 against 267 us at 28^3, N = 9)
+    constexpr int kFixedPF = sizeof(T) == 8 && N1 >= 10 ? 2 : N1;
+#define SEM_AXL(MODE, VT, PF, HELM)                                                            \
+    do {                                                                                       \
+        if (early)                                                                             \
+            hipLaunchKernelGGL((k_ax<N1, GS, MODE, VT, PF, HELM, (sizeof(GS) < 8)>), g, b, lds, \
+                               s, P);                                                          \
+        else                                                                                   \
+            hipLaunchKernelGGL((k_ax<N1, GS, MODE, VT, PF, HELM, false>), g, b, lds, s, P);     \
+    } while (0)
     if (c->helm) {
         // Helmholtz: FP64/FP32 factors, atomic summation on unique vectors
         if constexpr (sizeof(GS) >= 4) {
             // (FP64 vectors are the operator's own for FP64 factors)
             if (in_local || out_mode != OUT_ATOMIC || (vec64 && !std::is_same<T, double>::value))
                 return hipErrorInvalidValue;
-            if (ring)
-                hipLaunchKernelGGL((k_ax<N1, GS, MODE_ATOMIC, T, 2, true>), dim3((unsigned)grid),
-                                   dim3(threads), lds, s, P);
-            else
-                hipLaunchKernelGGL((k_ax<N1, GS, MODE_ATOMIC, T, N1, true>), dim3((unsigned)grid),
-                                   dim3(threads), lds, s, P);
-            if (partials)
-                hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, (int)FIN_AX,
-                                   (const double *)partials, (int)grid, st);
-            return hipGetLastError();
+            if (ring) SEM_AXL(MODE_ATOMIC, T, 2, true);
+            else SEM_AXL(MODE_ATOMIC, T, N1, true);
         } else {
             return hipErrorInvalidValue;
         }
-    }
-    if constexpr (MFMA32_OK) {
-        if (mfma32) {
-            if (vec64)
-                hipLaunchKernelGGL((k_ax_mfma32<GS, double>), dim3((unsigned)grid), dim3(threads),
-                                   lds, s, P);
-            else
-                hipLaunchKernelGGL((k_ax_mfma32<GS, float>), dim3((unsigned)grid), dim3(threads),
-                                   lds, s, P);
-            if (partials)
-                hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, (int)FIN_AX,
-                                   (const double *)partials, (int)grid, st);
-            return hipGetLastError();
+    } else if (mfma32) {
+        if constexpr (MFMA32_OK) {
+            if (vec64 && early) hipLaunchKernelGGL((k_ax_mfma32<GS, double, true>), g, b, lds, s, P);
+            else if (vec64) hipLaunchKernelGGL((k_ax_mfma32<GS, double, false>), g, b, lds, s, P);
+            else if (early) hipLaunchKernelGGL((k_ax_mfma32<GS, float, true>), g, b, lds, s, P);
+            else hipLaunchKernelGGL((k_ax_mfma32<GS, float, false>), g, b, lds, s, P);
         }
-    }
-    if constexpr (MFMA_OK) {
-        if (mfma) {
-            if (vec64)
-                hipLaunchKernelGGL((k_ax_mfma<GS, double>), dim3((unsigned)grid), dim3(threads),
-                                   lds, s, P);
-            else
-                hipLaunchKernelGGL((k_ax_mfma<GS, float>), dim3((unsigned)grid), dim3(threads),
-                                   lds, s, P);
-            if (partials)
-                hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, (int)FIN_AX,
-                                   (const double *)partials, (int)grid, st);
-            return hipGetLastError();
+    } else if (mfma) {
+        if constexpr (MFMA_OK) {
+            if (vec64) hipLaunchKernelGGL((k_ax_mfma<GS, double>), g, b, lds, s, P);
+            else hipLaunchKernelGGL((k_ax_mfma<GS, float>), g, b, lds, s, P);
         }
-    }
-    if (vec64 && !std::is_same<T, double>::value) {
+    } else if (vec64 && !std::is_same<T, double>::value) {
         if (in_local || out_mode != OUT_ATOMIC) return hipErrorInvalidValue;
-        if (ring)
-            hipLaunchKernelGGL((k_ax<N1, GS, MODE_ATOMIC, double, 2>), dim3((unsigned)grid),
-                               dim3(threads), lds, s, P);
-        else
-            hipLaunchKernelGGL((k_ax<N1, GS, MODE_ATOMIC, double>), dim3((unsigned)grid),
-                               dim3(threads), lds, s, P);
+        if (ring) SEM_AXL(MODE_ATOMIC, double, 2, false);
+        else SEM_AXL(MODE_ATOMIC, double, N1, false);
     } else if (in_local) {
-        hipLaunchKernelGGL((k_ax<N1, GS, MODE_LOCAL, T>), dim3((unsigned)grid), dim3(threads), lds,
-                           s, P);
+        SEM_AXL(MODE_LOCAL, T, kFixedPF, false);
     } else if (out_mode == OUT_COMPACT) {
-        hipLaunchKernelGGL((k_ax<N1, GS, MODE_COMPACT, T>), dim3((unsigned)grid), dim3(threads),
-                           lds, s, P);
+        SEM_AXL(MODE_COMPACT, T, kFixedPF, false);
     } else if (ring) {
-        hipLaunchKernelGGL((k_ax<N1, GS, MODE_ATOMIC, T, 2>), dim3((unsigned)grid), dim3(threads),
-                           lds, s, P);
+        SEM_AXL(MODE_ATOMIC, T, 2, false);
     } else {
-        hipLaunchKernelGGL((k_ax<N1, GS, MODE_ATOMIC, T>), dim3((unsigned)grid), dim3(threads),
-                           lds, s, P);
+        SEM_AXL(MODE_ATOMIC, T, N1, false);
     }
+#undef SEM_AXL
     if (partials)
         hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, (int)FIN_AX,
                            (const double *)partials, (int)grid, st);
@@ -1607,6 +1646,8 @@ struct BatchArgs {
 // largest orders keeps them at two waves per SIMD
 template <int N1>
 constexpr int kBatchPF = N1 >= 9 ? 2 : N1;
+template <typename T>
+constexpr bool kBatchEarly = sizeof(T) < 8;
 
 template <int N1, typename T>
 __device__ __forceinline__ void batch_group(const BatchArgs &A, const BatchProb &pb,
@@ -1631,17 +1672,20 @@ __device__ __forceinline__ void batch_group(const BatchArgs &A, const BatchProb 
         in = pb.p32;
         out = pb.w32;
     }
-    fill_dl<N1, T>(Dl, D);
     const int64_t e = group * pb.epb + L.slot;
     const bool active = L.slot < pb.epb && e < pb.E;
     const int64_t ec = active ? e : 0;
     AxMesh<T> M{in, out, nullptr, reinterpret_cast<const T *>(G), nullptr,
                 pb.bmap, pb.E, pb.n_bnd, 0, OUT_ATOMIC, nullptr, 1.0, 0.0};
     int32_t bm[N1];
+    Fac<T> g[kFacRegs<N1, kBatchPF<N1>>];
     load_map<N1>(pb.bmap, L, ec, bm);
+    const T d = threadIdx.x < N1 * N1 ? D[threadIdx.x] : T(0);
+    if (kBatchEarly<T>) load_factors<N1, T, kBatchPF<N1>>(M.G, ec, L.col, g);
+    if (threadIdx.x < N1 * N1) Dl[threadIdx.x] = d;
     __syncthreads();
-    ax_element<N1, T, MODE_ATOMIC, T, kBatchPF<N1>>(M, D, DT, Dl, L, S0, ec, active, -1, bm, true,
-                                                    dot);
+    ax_element<N1, T, MODE_ATOMIC, T, kBatchPF<N1>, false, kBatchEarly<T>>(M, D, DT, Dl, L, S0, ec, active,
+                                                                 -1, bm, g, true, dot);
 }
 
 // Operator pass over the work items [lo, hi) of the problems of one order:

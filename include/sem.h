@@ -256,7 +256,7 @@ typedef struct {
                                      factors at N = 7; sem_autotune tries it
                                      for each of them. Pipelines 2 and 3
                                      apply to the atomic assembled operator;
-                                     the other forms use pipeline 0.         */
+                                     the other forms do not depend on it.    */
 } sem_tile;
 
 typedef struct {

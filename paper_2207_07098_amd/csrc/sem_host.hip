@@ -110,6 +110,38 @@ extern "C" const char *sem_last_error(sem_ctx ctx) {
     return ctx ? ctx->err.c_str() : g_last_error.c_str();
 }
 
+// Launch shape of the element operator before any sem_autotune, from timings
+// of every shape at N = 2..13 and 0.3, 2 and 16 million nodes (times below at
+// 16 million, FP64 unless another type is named; us):
+//  * one workgroup per element group and no XCD remap throughout (48^3, N = 7:
+//    623 against 690 remapped);
+//  * FP64: small elements share a workgroup -- N = 2 eight per workgroup (1066
+//    against 1659 for one), N = 3 and 4 two (725 / 383 against 828 / 502),
+//    N = 5 three (343 against 394; seven: 349), N = 6 one (296; two: 299),
+//    N = 7 one up to 32768 elements (24^3: 83 against 88 for two) and two from
+//    there (48^3: 621 against 662);
+//  * 32- and 16-bit factors: N = 2 four (695 against 1090), N = 3 to 7 one (N
+//    = 5: 221 in FP32 against 309 for seven);
+//  * N = 8: 81 lanes leave 47 of a second wave idle, three elements 13 of
+//    four waves (FP64 249 against 278, FP32 146 against 157), except on few
+//    elements, where the launch is latency (512: 12.2 against 12.5);
+//  * FP64 from N = 8 and FP32 from N = 11: a ring of two factor planes (N = 9:
+//    267 against 439; N = 11 in FP32: 148 against 173).
+static AxTile default_tile(int N, int64_t E, int prec) {
+    AxTile t;
+    t.xcd = 0;
+    const bool f64 = prec == SEM_FP64;
+    if (N == 1) t.epb = 16;
+    else if (N == 2) t.epb = f64 ? 8 : 4;
+    else if (N <= 4) t.epb = f64 ? 2 : 1;
+    else if (N == 5) t.epb = f64 ? 3 : 1;
+    else if (N == 7) t.epb = f64 && E >= 32768 ? 2 : 1;
+    else if (N == 8) t.epb = E >= 2048 ? 3 : 1;
+    else t.epb = 1;
+    t.pipeline = (f64 && N >= 8) || (prec == SEM_FP32 && N >= 11) ? 1 : 0;
+    return t;
+}
+
 extern "C" sem_status sem_setup(const sem_mesh *mesh, int N, const sem_options *opts,
                                 sem_ctx *out) {
     if (!mesh || !out) return fail(nullptr, SEM_ERR_INVALID, "null argument");
@@ -156,10 +188,7 @@ extern "C" sem_status sem_setup(const sem_mesh *mesh, int N, const sem_options *
     if (mesh->face_bc) c->face_bc.assign(mesh->face_bc, mesh->face_bc + 6 * c->E);
     else c->face_bc.assign(6 * c->E, 0);
     c->num_vertices = mesh->num_vertices;
-    for (int p = 0; p < kNumPrec; ++p) {
-        c->tile[p].epb = std::max(1, 64 / (c->n1 * c->n1));
-        if (c->n1 * c->n1 * c->tile[p].epb < 64 && c->n1 <= 6) c->tile[p].epb = 256 / (c->n1 * c->n1);
-    }
+    for (int p = 0; p < kNumPrec; ++p) c->tile[p] = default_tile(N, c->E, p);
     *out = c;
     return SEM_OK;
 }

@@ -17,10 +17,10 @@
 //    precision of the vectors (FP32 tables for the inner FP32 solves).
 //  * Additive combination with counting weights W (1 / number of subdomains
 //    holding the node).
-//  * Coarse grid: the N = 1 operator of the same library on the element
-//    vertices (its own context), trilinear interpolation P and restriction
-//    P^T (summed in the local-solve gather when both parts run), 10
-//    Jacobi-PCG iterations from zero.
+//  * Coarse grid: the N = 1 operator on the element vertices (its own
+//    context), trilinear interpolation P and restriction P^T (summed in the
+//    local-solve gather when both parts run), 10 Jacobi-PCG iterations from
+//    zero on the assembled operator (sem_coarse.hip).
 //  * Flexible GMRES(m) (the coarse PCG makes the preconditioner nonlinear):
 //    Arnoldi with classical Gram-Schmidt twice, the second projection of
 //    each new vector delayed to the next step (two sweeps over the basis
@@ -40,7 +40,9 @@
 #include <type_traits>
 #include <unordered_map>
 
+#include "sem_coarse.h"
 #include "sem_internal.h"
+#include "sem_reduce.h"
 
 using namespace sem;
 
@@ -466,16 +468,24 @@ __global__ void __launch_bounds__(64) k_combine_e(CoarseParams<VT> P) {
     }
 }
 
-// out[i] = sum over blocks of part[b][i], i < m
-__global__ void __launch_bounds__(kGmBlock) k_gm_finish(int nblocks, int m,
+// out[i] = sum over blocks of part[i][b] for i = blockIdx.x: one workgroup per
+// value (a single workgroup that took the values in turn needed 20 us for 40
+// values of 700 blocks, this form 4 us).
+__global__ void __launch_bounds__(kGmBlock) k_gm_finish(int nblocks,
                                                         const double *__restrict__ part,
                                                         double *__restrict__ out) {
     __shared__ double red[kGmBlock / 64];
-    for (int i = 0; i < m; ++i) {
-        double s = 0.0;
-        for (int b = threadIdx.x; b < nblocks; b += blockDim.x) s += part[(size_t)b * m + i];
-        s = gm_block_sum(s, red);
-        if (threadIdx.x == 0) out[i] = s;
+    const double *p = part + (size_t)blockIdx.x * nblocks;
+    double s = 0.0;
+    for (int b = threadIdx.x; b < nblocks; b += kGmBlock) s += p[b];
+    s = wave_sum63(s);
+    if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s = red[0];
+#pragma unroll
+        for (int w = 1; w < kGmBlock / 64; ++w) s += red[w];
+        out[blockIdx.x] = s;
     }
 }
 
@@ -503,13 +513,24 @@ template <typename T> struct PairOf;
 template <> struct PairOf<double> { using type = double2; };
 template <> struct PairOf<float> { using type = float2; };
 
-// Block sums of acc[0..L] into part[blk][0..L].
-template <int L>
-__device__ __forceinline__ void gm_store_sums(const double *acc, double *part, double *red) {
+// Block sums of acc[0..M) into part[i][blk]: every wave sums its lanes, one
+// barrier, then one lane per value adds the waves' sums.
+template <int M>
+__device__ __forceinline__ void gm_store_sums(const double *acc, double *part) {
+    constexpr int NW = kGmBlock / 64;
+    __shared__ double red[NW][M];
+    const int wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int i = 0; i <= L; ++i) {
-        const double sum = gm_block_sum(acc[i], red);
-        if (threadIdx.x == 0) part[(size_t)blockIdx.x * (L + 1) + i] = sum;
+    for (int i = 0; i < M; ++i) {
+        const double sum = wave_sum63(acc[i]);
+        if ((threadIdx.x & 63) == 63) red[wv][i] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x < M) {
+        double s = red[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s += red[w][threadIdx.x];
+        part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = s;
     }
 }
 
@@ -528,14 +549,12 @@ __device__ __forceinline__ void gm_st(typename NtPair<T>::type v, T *base, int64
     __builtin_nontemporal_store(v, reinterpret_cast<typename NtPair<T>::type *>(base) + p);
 }
 
-// part[blk][i] = X_i . v (i < L), part[blk][L] = v . v
+// part[i][blk] = X_i . v (i < L), part[L][blk] = v . v
 template <int L, typename T>
 __global__ void __launch_bounds__(kGmBlock) k_gm_dots(int64_t n, int64_t ld,
                                                       const T *__restrict__ X,
                                                       const T *__restrict__ v,
                                                       double *__restrict__ part) {
-    using P = typename PairOf<T>::type;
-    __shared__ double red[kGmBlock / 64];
     double acc[L + 1];
 #pragma unroll
     for (int i = 0; i <= L; ++i) acc[i] = 0.0;
@@ -556,7 +575,7 @@ __global__ void __launch_bounds__(kGmBlock) k_gm_dots(int64_t n, int64_t ld,
         for (int i = 0; i < L; ++i) acc[i] += (double)X[i * ld + n - 1] * vq;
         acc[L] += vq * vq;
     }
-    gm_store_sums<L>(acc, part, red);
+    gm_store_sums<L + 1>(acc, part);
 }
 
 // x += sum_{i<L} y_i Z_i at the end of a cycle (y = coef[0..L)), summed in
@@ -596,16 +615,14 @@ __global__ void __launch_bounds__(kGmBlock) k_gm_xupd(int64_t n, int64_t ld,
 // At step j the basis V_0..V_{L-1} (L = j) is final and slot j holds the
 // once-projected, roughly normalised vector vt; w = A z with z the search
 // direction computed from vt.  One sweep forms all inner products
-//   part[blk] = [ X_i . vt (i < L), X_i . w (i < L), vt.vt, vt.w, w.w ].
+//   part[.][blk] = [ X_i . vt (i < L), X_i . w (i < L), vt.vt, vt.w, w.w ].
 template <int L, typename T>
 __global__ void __launch_bounds__(kGmBlock) k_gm_dots2(int64_t n, int64_t ld,
                                                        const T *__restrict__ X,
                                                        const T *__restrict__ vt,
                                                        const T *__restrict__ w,
                                                        double *__restrict__ part) {
-    using P = typename PairOf<T>::type;
     constexpr int M = 2 * L + 3;
-    __shared__ double red[kGmBlock / 64];
     double acc[M];
 #pragma unroll
     for (int i = 0; i < M; ++i) acc[i] = 0.0;
@@ -637,7 +654,7 @@ __global__ void __launch_bounds__(kGmBlock) k_gm_dots2(int64_t n, int64_t ld,
         acc[2 * L + 1] += v0 * w0;
         acc[2 * L + 2] += w0 * w0;
     }
-    gm_store_sums<M - 1>(acc, part, red);
+    gm_store_sums<M>(acc, part);
 }
 
 // Scalars of the delayed step from the sums d = [q (L), p (L), r, s, t]
@@ -875,6 +892,7 @@ struct sem_gmres_s {
     char *ws = nullptr;
     size_t ws_bytes = 0;
     size_t coarse_ws = 0;
+    CoarsePlan cplan;                // assembled coarse operator and its solve
     double *dS = nullptr, *dlam = nullptr, *dW = nullptr, *dxi = nullptr;
     float *dS32 = nullptr, *dlam32 = nullptr;   // FP32 copies (reduced precisions only)
     int32_t *dghost = nullptr, *dcmap = nullptr;
@@ -1110,7 +1128,7 @@ extern "C" sem_status sem_gmres_create(sem_ctx c, int restart, sem_gmres *out) {
     m0.face_bc = c->face_bc.data();
     m0.num_vertices = c->num_vertices;
     m0.vertex_xyz = nullptr;
-    sem_options o0{SEM_PREC_BIT(SEM_FP64), 1};
+    sem_options o0{SEM_PREC_BIT(SEM_FP64), 0};
     sem_status st = sem_setup(&m0, 1, &o0, &G->coarse);
     if (st) {
         const std::string msg = std::string("coarse grid: ") + sem_last_error(nullptr);
@@ -1123,6 +1141,7 @@ extern "C" sem_status sem_gmres_create(sem_ctx c, int restart, sem_gmres *out) {
         delete G;
         return fail(c, st, "coarse grid workspace");
     }
+    coarse_pattern(G->coarse, G->cplan);
     st = build_local(G);
     if (st) {
         sem_free(G->coarse);
@@ -1175,7 +1194,7 @@ static size_t gm_layout(sem_gmres G, size_t *off) {
     off[11] = take(8 * (size_t)G->ld * G->m);         // Z
     off[12] = take(8 * (size_t)c->n_unique);          // w
     off[13] = take(8 * (size_t)c->n_unique);          // r
-    off[14] = take(8 * (size_t)kGmGrid * (kGmMaxVec + 1));
+    off[14] = take(8 * (size_t)kGmGrid * (2 * kGmMaxVec + 3));   // partial sums, at most 2 L + 3 per block
     off[15] = take(8 * kGmCoef);
     off[16] = take(4 * (size_t)c->n_unique);          // FP32 inner right-hand side
     off[17] = take(4 * (size_t)c->n_unique);          // FP32 inner correction
@@ -1186,12 +1205,13 @@ static size_t gm_layout(sem_gmres G, size_t *off) {
     const bool low = (c->precisions & ~SEM_PREC_BIT(SEM_FP64)) != 0;
     off[21] = take(low ? 4 * (size_t)E * 3 * NE * NE : 0);
     off[22] = take(low ? 4 * (size_t)E * 3 * NE : 0);
+    off[23] = take(coarse_bytes(G->cplan));
     return o;
 }
 
 extern "C" sem_status sem_gmres_workspace_size(sem_gmres G, size_t *bytes) {
     if (!G || !bytes) return gfail(G, SEM_ERR_INVALID, "null argument");
-    size_t off[23];
+    size_t off[24];
     *bytes = gm_layout(G, off);
     return SEM_OK;
 }
@@ -1199,7 +1219,7 @@ extern "C" sem_status sem_gmres_workspace_size(sem_gmres G, size_t *bytes) {
 extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t bytes,
                                                sem_stream stream) {
     if (!G || !dev) return gfail(G, SEM_ERR_INVALID, "null argument");
-    size_t off[23];
+    size_t off[24];
     const size_t need = gm_layout(G, off);
     if (bytes < need)
         return gfail(G, SEM_ERR_OOM, "workspace of " + std::to_string(bytes) + " bytes, need " +
@@ -1235,6 +1255,7 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
     G->downer = reinterpret_cast<uint8_t *>(w + off[18]);
     G->dfmap = reinterpret_cast<int32_t *>(w + off[19]);
     G->down = reinterpret_cast<uint16_t *>(w + off[20]);
+    SEM_HIP(c, coarse_bind(G->coarse, G->cplan, w + off[23], G->b0, G->x0, s));
     SEM_HIP(c, hipMemcpyAsync(G->dS, G->S.data(), 8 * G->S.size(), hipMemcpyHostToDevice, s));
     SEM_HIP(c, hipMemcpyAsync(G->dlam, G->lam.data(), 8 * G->lam.size(), hipMemcpyHostToDevice, s));
     G->dS32 = G->dlam32 = nullptr;
@@ -1282,7 +1303,6 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
     // with both parts the coarse restriction is summed in the local-solve
     // kernel's gather (the residual is read once)
     const bool fused = local && coarse;
-    if (coarse) SEM_HIP(c, launch_fill(G->b0, G->coarse->n_unique, 0.0, s));
     // the Schwarz sum in the vectors' precision (an FP32 sum uses the first
     // half of the FP64 buffer)
     VT *zs = reinterpret_cast<VT *>(G->zs);
@@ -1341,17 +1361,9 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
         }
 #undef SEM_RESTRICT
         SEM_HIP(c, hipGetLastError());
-        // 10 Jacobi-PCG iterations from zero on the coarse operator
-        sem_solve_options o;
-        sem_default_solve_options(&o);
-        o.tol = 1e-14;
-        o.max_iter = 10;
-        o.max_restart = 0;
-        o.check_every = 10;
-        sem_solve_info inf;
-        const sem_status st = sem_cg_solve(G->coarse, G->b0, G->x0, &o, &inf, s);
-        if (st != SEM_OK && st != SEM_ERR_NOT_CONVERGED && st != SEM_ERR_BREAKDOWN)
-            return gfail(G, st, std::string("coarse solve: ") + sem_last_error(G->coarse));
+        // 10 Jacobi-PCG iterations from zero on the coarse operator (which
+        // leave b0 cleared for the next application)
+        SEM_HIP(c, coarse_solve(G->cplan, s));
     } else {
         C.x0 = nullptr;
     }
@@ -1375,7 +1387,15 @@ extern "C" sem_status sem_gmres_precondition(sem_gmres G, const double *r, doubl
     if (!G->ws) return gfail(G, SEM_ERR_STATE, "no workspace bound");
     if (!(parts & (SEM_PC_SCHWARZ | SEM_PC_COARSE)) || (parts & ~3u))
         return gfail(G, SEM_ERR_INVALID, "parts must name SEM_PC_SCHWARZ and/or SEM_PC_COARSE");
-    return precondition<double>(G, r, z, parts, (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    const sem_status st = precondition<double>(G, r, z, parts, s);
+    if (st || !(parts & SEM_PC_COARSE)) return st;
+    CgState cs;
+    SEM_HIP(G->ctx, hipMemcpyAsync(&cs, coarse_result(G->cplan), sizeof(cs), hipMemcpyDeviceToHost, s));
+    SEM_HIP(G->ctx, hipStreamSynchronize(s));
+    if (cs.status == CG_NONFINITE)
+        return gfail(G, SEM_ERR_NAN, "coarse solve: FP64 PCG met a non-finite value");
+    return SEM_OK;
 }
 
 // y = A x with the operator of precision prec (FP64 vectors for SEM_FP64,
@@ -1416,7 +1436,7 @@ struct GmDots {
         const int64_t n = G->ctx->n_unique;
         const unsigned g = resident_grid(k_gm_dots<L, T>, per_cu, G->ctx->num_cus, n / 2);
         hipLaunchKernelGGL((k_gm_dots<L, T>), dim3(g), dim3(kGmBlock), 0, s, n, G->ld, X, v, G->part);
-        hipLaunchKernelGGL(k_gm_finish, dim3(1), dim3(kGmBlock), 0, s, (int)g, L + 1,
+        hipLaunchKernelGGL(k_gm_finish, dim3(L + 1), dim3(kGmBlock), 0, s, (int)g,
                            (const double *)G->part, G->coef);
         return hipGetLastError();
     }
@@ -1444,7 +1464,7 @@ struct GmDots2 {
         const unsigned g = resident_grid(k_gm_dots2<L, T>, per_cu, G->ctx->num_cus, n / 2);
         hipLaunchKernelGGL((k_gm_dots2<L, T>), dim3(g), dim3(kGmBlock), 0, s, n, G->ld, X, vt, w,
                            G->part);
-        hipLaunchKernelGGL(k_gm_finish, dim3(1), dim3(kGmBlock), 0, s, (int)g, 2 * L + 3,
+        hipLaunchKernelGGL(k_gm_finish, dim3(2 * L + 3), dim3(kGmBlock), 0, s, (int)g,
                            (const double *)G->part, G->coef + kGmD);
         return hipGetLastError();
     }
@@ -1483,7 +1503,7 @@ static hipError_t gm_norm2(sem_gmres G, const T *v, hipStream_t s) {
     const int64_t n = G->ctx->n_unique;
     const unsigned g = resident_grid(k_gm_norm2<T>, per_cu, G->ctx->num_cus, n);
     hipLaunchKernelGGL(k_gm_norm2<T>, dim3(g), dim3(kGmBlock), 0, s, n, v, G->part);
-    hipLaunchKernelGGL(k_gm_finish, dim3(1), dim3(kGmBlock), 0, s, (int)g, 1, (const double *)G->part,
+    hipLaunchKernelGGL(k_gm_finish, dim3(1), dim3(kGmBlock), 0, s, (int)g, (const double *)G->part,
                        G->coef);
     return hipGetLastError();
 }

@@ -447,9 +447,9 @@ sem_status sem_proj_solve(sem_proj proj, const double *b, double *x,
  * The context must have geometry and opts.solver = 1, 2 <= N <= 13, and the
  * Poisson operator (SEM_ERR_UNSUPPORTED for a Helmholtz pair).  The solver
  * owns an internal N = 1 context (host data); device memory is one
- * caller-owned workspace (about (2 restart + 5) unique vectors, the
- * eigenvectors 3 (N+3)^2 and extension maps 6 (N+1)^2 per element, and the
- * coarse context's workspace).  sem_gmres_bind_workspace uploads the
+ * caller-owned workspace (about (2 restart + 4) unique vectors; per element
+ * the eigenvectors 3 (N+3)^2, the gather map (N+3)^3 and the local solution
+ * (N+1)^3 + 6 (N+1)^2; and the coarse context's workspace).  sem_gmres_bind_workspace uploads the
  * preconditioner and sets up the coarse geometry (synchronises `stream`).
  * sem_gmres_solve: b, x device unique vectors (solver order, FP64); opts:
  * tol (true relative residual, checked in FP64 at each restart), max_iter,

@@ -11,12 +11,11 @@
 //    and lumped mass M of the neighbour-element-neighbour line (mean edge
 //    lengths), solved by fast diagonalisation: per direction K S = M S Lambda
 //    (host, once), then u = S (Lambda_r + Lambda_s + Lambda_t)^-1 S^T r with
-//    three tensor contractions each way (a persistent kernel, one workgroup
-//    per element at a time, k-column in registers, r/s contractions through
-//    LDS, the box gathered through a map built at bind time), in the
+//    three tensor contractions each way on matrix cores (one element per
+//    wave, the box gathered through a map built at bind time), in the
 //    precision of the vectors (FP32 tables for the inner FP32 solves).
-//  * Additive combination with counting weights W (1 / number of subdomains
-//    holding the node).
+//  * Additive combination with counting weights (1 / number of subdomains
+//    holding the node): the boxes are stored whole and summed node by node.
 //  * Coarse grid: the N = 1 operator on the element vertices (its own
 //    context), trilinear interpolation P and restriction P^T (summed in the
 //    local-solve gather when both parts run), 10 Jacobi-PCG iterations from
@@ -115,7 +114,8 @@ __device__ __forceinline__ int64_t gm_node(const int32_t *bmap, int64_t n_bnd, i
 template <typename VT>
 struct FdmParams {
     const VT *r;              // residual (unique, solver order; FP64 or FP32)
-    VT *z;                    // sum of local solutions (atomic)
+    VT *o;                    // [E][BoxStore::SIZE] local solutions
+    const int32_t *at;        // [NE][NE^2] storage position of a box point or -1
     const VT *S;              // [E][3][NE][NE] eigenvectors S[a][m]
     const VT *lam;            // [E][3][NE]
     const int32_t *fmap;      // [E][NE][NE^2] box gather map: solver index or -1
@@ -127,7 +127,30 @@ struct FdmParams {
     const double *xi;         // GLL nodes [N+1]
 };
 
-// Box gather map of every element, built once when the workspace is bound:
+// Storage of an element's local solution: the values of its interior points
+// (solver order of the element interior), of its boundary points (order of the
+// element map), then of the six extension planes (p + n1 q each), so that the
+// sum reads contiguous runs; edges and corners of the extension carry no data.
+// Padded to whole 128-byte lines of FP64.
+template <int NE>
+struct BoxStore {
+    static constexpr int N = NE - 3, N1 = N + 1, NI = (N - 1) * (N - 1) * (N - 1),
+                         NB = N1 * N1 * N1 - NI, F2 = N1 * N1, SIZE = (NI + NB + 6 * F2 + 15) / 16 * 16;
+    // position of box point (a, b, c), -1 for the edges and corners
+    static __device__ int at(int a, int b, int c) {
+        const int i = a - 1, j = b - 1, k = c - 1;
+        const bool oi = i < 0 || i > N, oj = j < 0 || j > N, ok = k < 0 || k > N;
+        if (oi + oj + ok > 1) return -1;
+        if (oi) return NI + NB + (i < 0 ? 0 : 1) * F2 + j + N1 * k;
+        if (oj) return NI + NB + (j < 0 ? 2 : 3) * F2 + i + N1 * k;
+        if (ok) return NI + NB + (k < 0 ? 4 : 5) * F2 + i + N1 * j;
+        if (i == 0 || i == N || j == 0 || j == N || k == 0 || k == N) return NI + gm_bpos(i, j, k, N1);
+        return ((k - 1) * (N - 1) + (j - 1)) * (N - 1) + i - 1;
+    }
+};
+
+// Box gather map of every element, built once when the workspace is bound
+// (with the storage positions at[c][a + NE b] of a box):
 // fmap[e][c][a + NE b] = solver index of box point (a, b, c) (own points
 // through the element's map, one-layer extension through the face map),
 // -1 where the box holds no data (edges and corners of the extension).
@@ -135,11 +158,13 @@ template <int NE>
 __global__ void __launch_bounds__((NE * NE + 63) / 64 * 64)
 k_fdm_map(const int32_t *__restrict__ ghost, const int32_t *__restrict__ bmap,
           const uint8_t *__restrict__ owner, int64_t E, int64_t n_bnd, int nb,
-          int32_t *__restrict__ fmap, uint16_t *__restrict__ own) {
+          int32_t *__restrict__ fmap, uint16_t *__restrict__ own, int32_t *__restrict__ at) {
     constexpr int C = NE * NE, N = NE - 3, n1 = NE - 2;
     const int64_t e = blockIdx.x;
     const int t = threadIdx.x;
     if (t >= C || e >= E) return;
+    if (e == 0)
+        for (int c = 0; c < NE; ++c) at[c * C + t] = BoxStore<NE>::at(t % NE, t / NE, c);
     const int i = t % NE - 1, j = t / NE - 1;
     // owned own points of the column: interior points, and on the element
     // boundary the first copy of a non-Dirichlet node
@@ -172,196 +197,303 @@ k_fdm_map(const int32_t *__restrict__ ghost, const int32_t *__restrict__ bmap,
     }
 }
 
-// Box index a in 0..NE-1 <-> local index a - 1.  A lane owns the column
-// (a, b) of the box over c (k-direction) in registers.  Persistent over
-// elements: while element e is transformed, the gather indices and the
-// eigenvector tables of the next element are already being fetched, so an
-// element waits for one memory round trip (its residual values) instead of
-// three (map, then values; tables).  Register budget: three waves per SIMD
-// up to NE = 11 (FP32 residuals would otherwise take two), two above.
-// Waves per SIMD: FP64 three up to NE = 11 (a few spilled registers at
-// four), FP32 four up to NE = 10 (NE = 11 spills 29 registers at four).
+// Fast-diagonalisation solve on matrix cores, one element per wave.
+//
+// Each of the six contractions (S_t^T, S_s^T, S_r^T, then S_r, S_s, S_t) is a
+// NE x NE by NE x NE^2 product: 16x16x4 MFMAs with the matrix padded to 16
+// rows as operand A (lane: row lane % 16, column 4 s + lane / 16 in step s)
+// and 16 lines of the box per tile as operand B (lane: line lane % 16).  The
+// box is gathered straight into operand layout for the t-direction, passes
+// through one LDS buffer whenever the contracted direction changes ([index to
+// be contracted next][line], with pitches that keep the transposing writes
+// free of bank conflicts), and the r-direction's forward result is already the
+// operand of its backward pass (result row = the next contraction index; FP32
+// results lie at row 4 (lane / 16) + register, FP64 ones at 4 register + lane
+// / 16, and the operand A follows).  One wave per workgroup: its LDS
+// operations stay in order, so there are no barriers.
+//
+// What bounds it at NE = 10 in FP64: 126 MFMAs of 64 cycles per element (54% of
+// the kernel's SIMD cycles; 10 of 16 rows are used) and about 1150 vector
+// instructions (34%), which share the issue of three waves per SIMD; 1.9 GB of
+// maps, tables and box values at 48^3 are 0.3 ms.  0.78 ms there.  A lane that
+// held a column of the box and took every product on the vector ALUs read
+// one LDS operand per FMA, four times what LDS delivers, and added the result
+// with 99 million atomics: 2.02 ms (21x18x16, NE = 9 in FP32: 78 -> 33 us).  A
+// persistent form with the next element's map in flight kept 20 more
+// registers alive and spilled 54 of them at three waves (1.35 ms).
+template <int NE, typename VT>
+struct FdmShape {
+    static constexpr int C = NE * NE, T = (C + 15) / 16, KS = (NE + 3) / 4;
+    // Row pitch of the LDS buffer where a line's results go to row hi ([hi][lo
+    // + NE row]) and to row lo ([lo][row + NE hi]): the values for NE = 5..16
+    // that cost the fewest LDS cycles over the writes and reads of a pass with
+    // 16 (FP64) or 32 (FP32) lanes served per cycle (NE = 10 in FP64: 168 and
+    // 168 cycles, none lost to conflicts; a pitch of 112 for both: 198 and 563,
+    // and 62% of the LDS cycles counted as conflicts).
+    static constexpr int kHi64[12] = {37, 38, 55, 72, 89, 106, 123, 156, 173, 206, 239, 256};
+    static constexpr int kLo64[12] = {33, 41, 49, 65, 81, 105, 129, 145, 177, 201, 225, 257};
+    static constexpr int kHi32[12] = {25, 48, 80, 80, 112, 112, 144, 156, 176, 208, 240, 272};
+    static constexpr int kLo32[12] = {45, 39, 81, 85, 82, 105, 146, 149, 174, 211, 231, 275};
+    static constexpr int PHI = sizeof(VT) == 8 ? kHi64[NE - 5] : kHi32[NE - 5];
+    static constexpr int PLO = sizeof(VT) == 8 ? kLo64[NE - 5] : kLo32[NE - 5];
+    static constexpr int ROWS = NE * (PHI > PLO ? PHI : PLO);
+    static_assert(PHI >= C && PLO >= C, "a row holds all lines");
+};
+
+typedef double gm_d4 __attribute__((ext_vector_type(4)));
+typedef float gm_f4 __attribute__((ext_vector_type(4)));
+template <typename T> struct GmAcc;
+template <> struct GmAcc<double> {
+    using type = gm_d4;
+    static constexpr int QMUL = 1, RMUL = 4;        // result row = QMUL (lane / 16) + RMUL reg
+    static __device__ __forceinline__ gm_d4 mma(double a, double b, gm_d4 c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+};
+template <> struct GmAcc<float> {
+    using type = gm_f4;
+    static constexpr int QMUL = 4, RMUL = 1;
+    static __device__ __forceinline__ gm_f4 mma(float a, float b, gm_f4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+};
+
+// 1 / x to rounding for positive normal x (the hardware estimate and two
+// Newton steps; a division adds scaling for the ends of the exponent range).
+__device__ __forceinline__ double gm_inverse(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ float gm_inverse(float x) {
+    const float y = __builtin_amdgcn_rcpf(x);
+    return fmaf(fmaf(-x, y, 1.0f), y, y);
+}
+
+// Waves per SIMD the register budget allows for: operands and results of all
+// tiles are live at once (NE = 10: 7 tiles).
 template <int NE, typename VT>
 struct FdmOcc {
     static constexpr int value =
-        sizeof(VT) == 8 ? (NE <= 11 ? 3 : 2) : (NE <= 10 ? 4 : (NE <= 11 ? 3 : 2));
+        sizeof(VT) == 8 ? (NE <= 8 ? 5 : (NE <= 10 ? 3 : (NE <= 12 ? 2 : 1)))
+                        : (NE <= 8 ? 5 : (NE <= 10 ? 4 : (NE <= 12 ? 3 : (NE <= 14 ? 2 : 1))));
 };
 
 template <int NE, typename VT>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, (NE * NE + 63) / 64 * 64),
+__global__ void __attribute__((amdgpu_flat_work_group_size(64, 64),
                                amdgpu_waves_per_eu(FdmOcc<NE, VT>::value)))
 k_fdm(FdmParams<VT> P) {
-    constexpr int C = NE * NE, NT = (C + 63) / 64 * 64;
-    constexpr int QS = (3 * C + NT - 1) / NT, QL = (3 * NE + NT - 1) / NT;
-    __shared__ VT Sl[3][C];
-    __shared__ VT Ll[3][NE];
-    __shared__ VT box[NE][NE][NE + 1];            // [c][b][a], padded
-    __shared__ double red8[NT / 64][8];            // restriction: per-wave corner sums
-    const int t = threadIdx.x;
-    const bool lane_on = t < C;
-    const int a = t % NE, b = t / NE;
-    // restriction weights of the lane's column in r and s: the linear shape
-    // functions of the element corners at the GLL node (zero off the element)
-    double wab[4] = {0.0, 0.0, 0.0, 0.0};
-    if (P.b0 && lane_on && a >= 1 && a <= NE - 2 && b >= 1 && b <= NE - 2) {
-        const double xa = P.xi[a - 1], xb = P.xi[b - 1];
-        const double fa[2] = {0.5 * (1.0 - xa), 0.5 * (1.0 + xa)};
-        const double fb[2] = {0.5 * (1.0 - xb), 0.5 * (1.0 + xb)};
+    using Sh = FdmShape<NE, VT>;
+    using A = GmAcc<VT>;
+    using Acc = typename A::type;
+    constexpr int C = Sh::C, T = Sh::T, KS = Sh::KS;
+    constexpr int NR = A::RMUL == 4 ? KS : 4;       // result registers that hold rows < NE
+    constexpr int QS = (3 * C + 63) / 64;
+    // + 64: results of padded rows and lines, and what the last tile's reads
+    // of the last row go beyond it
+    __shared__ VT buf[Sh::ROWS + 64];
+    __shared__ VT Sl[3 * C];
+    __shared__ VT lams[3][NE];
+    __shared__ double phi[2][NE];                   // coarse shape functions at the box points
+    const int64_t e = blockIdx.x;
+    const int lane = threadIdx.x, j = lane & 15, q = lane >> 4;
+    // ---- gather map, eigenvectors and eigenvalues of the element
+    int32_t idx[T][KS];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) wab[q] = fa[q & 1] * fb[q >> 1];
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int col = 16 * t + j, k = 4 * s + q;
+            const bool ok = col < C && k < NE;
+            const int32_t m = __builtin_nontemporal_load(
+                P.fmap + ((size_t)e * NE + (k < NE ? k : NE - 1)) * C + (col < C ? col : C - 1));
+            idx[t][s] = ok ? m : -1;
+        }
+    VT sr[QS];
+#pragma unroll
+    for (int x = 0; x < QS; ++x)
+        sr[x] = __builtin_nontemporal_load(P.S + (size_t)e * 3 * C + min(lane + 64 * x, 3 * C - 1));
+    const VT lr0 = P.lam[(size_t)e * 3 * NE + min(lane, 3 * NE - 1)];
+    int32_t corner = -1;                            // of the lane's element corner (lane < 8)
+    uint32_t own[T];
+    if (P.b0) {
+        corner = P.cmap[e * 8 + (lane & 7)];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int col = 16 * t + j;
+            const uint32_t m = P.own[(size_t)e * C + (col < C ? col : C - 1)];
+            own[t] = col < C ? m : 0u;
+        }
+        if (lane < NE) {
+            const bool in = lane >= 1 && lane <= NE - 2;
+            const double x = P.xi[in ? lane - 1 : 0];
+            phi[0][lane] = in ? 0.5 * (1.0 - x) : 0.0;
+            phi[1][lane] = in ? 0.5 * (1.0 + x) : 0.0;
+        }
     }
-    int32_t idx[NE], nidx[NE];
-    VT sreg[QS], lreg[QL];
-    auto fetch = [&](int64_t e, int32_t (&ix)[NE], VT (&sr)[QS], VT (&lr)[QL]) {
-        const bool ok = e < P.E;
+    __builtin_amdgcn_wave_barrier();
+    VT v[T][KS];
 #pragma unroll
-        for (int c = 0; c < NE; ++c)
-            ix[c] = (lane_on && ok) ? __builtin_nontemporal_load(P.fmap + ((size_t)e * NE + c) * C + t) : -1;
+    for (int t = 0; t < T; ++t)
 #pragma unroll
-        for (int q = 0; q < QS; ++q) {
-            const int x = t + q * NT;
-            sr[q] = (ok && x < 3 * C) ? __builtin_nontemporal_load(P.S + (size_t)e * 3 * C + x) : VT(0);
+        for (int s = 0; s < KS; ++s) {
+            const VT x = P.r[idx[t][s] >= 0 ? idx[t][s] : 0];
+            v[t][s] = idx[t][s] >= 0 ? x : VT(0);
         }
 #pragma unroll
-        for (int q = 0; q < QL; ++q) {
-            const int x = t + q * NT;
-            lr[q] = (ok && x < 3 * NE) ? P.lam[(size_t)e * 3 * NE + x] : VT(0);
+    for (int x = 0; x < QS; ++x)
+        if (lane + 64 * x < 3 * C) Sl[lane + 64 * x] = sr[x];
+    if (lane < 3 * NE) lams[lane / NE][lane % NE] = lr0;
+    __builtin_amdgcn_wave_barrier();
+    // ---- P^T r over the element's owned points: the t-shape functions on the
+    // lane's points, then the r and s ones, one wave sum per corner
+    if (P.b0) {
+        double cs[8] = {};
+        double p0[KS], p1[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int k = 4 * s + q, kc = k < NE ? k : NE - 1;   // phi is zero at NE - 1
+            p0[s] = phi[0][kc];
+            p1[s] = phi[1][kc];
         }
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int col = 16 * t + j, a = col % NE, b = col / NE;
+            double x0 = 0.0, x1 = 0.0;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const double vc = ((own[t] >> (4 * s + q)) & 1u) ? (double)v[t][s] : 0.0;
+                x0 += p0[s] * vc;
+                x1 += p1[s] * vc;
+            }
+            const int bc = b < NE ? b : NE - 1;
+            const double fa0 = phi[0][a], fa1 = phi[1][a], fb0 = phi[0][bc], fb1 = phi[1][bc];
+            const double y[4] = {fb0 * x0, fb1 * x0, fb0 * x1, fb1 * x1};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                cs[2 * u] += fa0 * y[u];
+                cs[2 * u + 1] += fa1 * y[u];
+            }
+        }
+        // corner u's sum from lane 63 to lane u: one atomic instruction
+        double mine = 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const double sum = wave_total(cs[u]);
+            mine = lane == u ? sum : mine;
+        }
+        if (lane < 8 && corner >= 0) unsafeAtomicAdd(P.b0 + corner, mine);
+    }
+    // ---- contractions.  Line (lo, hi) of a tile; the LDS positions of its
+    // results for the next direction: w1 = [hi][lo + NE row], w2 = [lo][row + NE hi]
+    Acc acc[T];
+    // S_d^T (row = mode, contracted over points) or S_d (row = point)
+    const int jc = j < NE ? j : NE - 1;
+    auto contract = [&](int d, bool forward) {
+        VT a[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int k = 4 * s + q, kc = k < NE ? k : NE - 1;
+            const VT x = Sl[d * C + (forward ? kc * NE + jc : jc * NE + kc)];
+            a[s] = j < NE && k < NE ? x : VT(0);
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[t] = Acc{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = A::mma(a[s], v[t][s], acc[t]);
     };
-    fetch(blockIdx.x, idx, sreg, lreg);
-    for (int64_t e = blockIdx.x; e < P.E; e += gridDim.x) {
-        // gather the box column (zero where the box holds no data): one
-        // unconditional load per point from a valid address, masked after
-        VT v[NE];
+    auto put = [&](bool by_hi) {
 #pragma unroll
-        for (int c = 0; c < NE; ++c) v[c] = P.r[idx[c] >= 0 ? idx[c] : 0];
-        __syncthreads();                           // previous element done with LDS
+        for (int t = 0; t < T; ++t) {
+            const int col = 16 * t + j, lo = col % NE, hi = col / NE;
+            const int base = by_hi ? hi * Sh::PHI + lo : lo * Sh::PLO + NE * hi;
+            const int step = by_hi ? NE : 1;
 #pragma unroll
-        for (int q = 0; q < QS; ++q) {
-            const int x = t + q * NT;
-            if (x < 3 * C) Sl[x / C][x % C] = sreg[q];
-        }
-#pragma unroll
-        for (int q = 0; q < QL; ++q) {
-            const int x = t + q * NT;
-            if (x < 3 * NE) Ll[x / NE][x % NE] = lreg[q];
-        }
-        fetch(e + gridDim.x, nidx, sreg, lreg);   // next element, in flight meanwhile
-#pragma unroll
-        for (int c = 0; c < NE; ++c) v[c] = idx[c] >= 0 ? v[c] : VT(0);
-        if (P.b0) {
-            // P^T r over the element's owned points: sum over c of the t-shape
-            // functions times r, then the r, s weights; one wave sum per corner
-            const uint32_t om = lane_on ? P.own[(size_t)e * C + t] : 0u;
-            double t0 = 0.0, t1 = 0.0;
-#pragma unroll
-            for (int c = 1; c <= NE - 2; ++c) {
-                const double xc = P.xi[c - 1];
-                const double vc = ((om >> c) & 1u) ? (double)v[c] : 0.0;
-                t0 += 0.5 * (1.0 - xc) * vc;
-                t1 += 0.5 * (1.0 + xc) * vc;
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                double sum = wab[q & 3] * ((q & 4) ? t1 : t0);
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-                if ((t & 63) == 0) red8[t >> 6][q] = sum;
+            for (int r = 0; r < NR; ++r) {
+                const int row = A::QMUL * q + A::RMUL * r;
+                buf[col < C && row < NE ? base + step * row : Sh::ROWS + lane] = acc[t][r];
             }
         }
-        __syncthreads();
-        if (P.b0 && t == 0)
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto get = [&](bool by_hi) {
+        const int pitch = by_hi ? Sh::PHI : Sh::PLO;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                double sum = 0.0;
+        for (int s = 0; s < KS; ++s) {
+            const int k = 4 * s + q, kc = k < NE ? k : NE - 1;   // operand A is zero beyond NE
 #pragma unroll
-                for (int wv = 0; wv < NT / 64; ++wv) sum += red8[wv][q];
-                const int32_t gc = P.cmap[e * 8 + q];
-                if (gc >= 0) atomicAdd(P.b0 + gc, sum);
-            }
-        // forward: w = (S_t^T x S_s^T x S_r^T) v
-        VT w[NE];
-#pragma unroll
-        for (int m = 0; m < NE; ++m) {             // t-direction, register-local
-            VT acc = 0;
-#pragma unroll
-            for (int c = 0; c < NE; ++c) acc += Sl[2][c * NE + m] * v[c];
-            w[m] = acc;
+            for (int t = 0; t < T; ++t) v[t][s] = buf[kc * pitch + 16 * t + j];
         }
-        if (lane_on)
+        __builtin_amdgcn_wave_barrier();
+    };
+    contract(2, true);                              // t forward: lines (a, b)
+    put(true);
+    get(true);
+    contract(1, true);                              // s forward: lines (a, m_t)
+    put(false);
+    get(false);
+    contract(0, true);                              // r forward: lines (m_s, m_t)
+    {
+        const VT cut = VT(1e-13) * (lams[0][NE - 1] + lams[1][NE - 1] + lams[2][NE - 1]);
+        VT lr[NR], aR[NR];                          // S_r in the order of the result rows
 #pragma unroll
-            for (int c = 0; c < NE; ++c) box[c][b][a] = w[c];
-        __syncthreads();
-        VT w2[NE];
-        if (lane_on)                               // s-direction: lane (a, b) -> mode b
+        for (int r = 0; r < NR; ++r) {
+            const int row = A::QMUL * q + A::RMUL * r, rc = row < NE ? row : NE - 1;
+            lr[r] = lams[0][rc];
+            const VT x = Sl[jc * NE + rc];
+            aR[r] = j < NE && row < NE ? x : VT(0);
+        }
+        Acc in[T];
 #pragma unroll
-            for (int c = 0; c < NE; ++c) {
-                VT acc = 0;
-                for (int bb = 0; bb < NE; ++bb) acc += Sl[1][bb * NE + b] * box[c][bb][a];
-                w2[c] = acc;
-            }
-        __syncthreads();
-        if (lane_on)
+        for (int t = 0; t < T; ++t) {
+            const int col = 16 * t + j, lo = col % NE, hi = col / NE < NE ? col / NE : NE - 1;
+            const VT ls = lams[1][lo] + lams[2][hi];
+            // a zero sum only for an element without any neighbour or
+            // Dirichlet face (its constant mode): pseudo-inverse
 #pragma unroll
-            for (int c = 0; c < NE; ++c) box[c][b][a] = w2[c];
-        __syncthreads();
-        if (lane_on)                               // r-direction: lane (a, b) -> mode a
-#pragma unroll
-            for (int c = 0; c < NE; ++c) {
-                VT acc = 0;
-                for (int aa = 0; aa < NE; ++aa) acc += Sl[0][aa * NE + a] * box[c][b][aa];
-                const VT lsum = Ll[0][a] + Ll[1][b] + Ll[2][c];
-                // a zero sum only for an element without any neighbour or
-                // Dirichlet face (its constant mode): pseudo-inverse
-                w2[c] = lsum > VT(1e-13) * (Ll[0][NE - 1] + Ll[1][NE - 1] + Ll[2][NE - 1]) ? acc / lsum
-                                                                                         : VT(0);
-            }
-        __syncthreads();
-        if (lane_on)
-#pragma unroll
-            for (int c = 0; c < NE; ++c) box[c][b][a] = w2[c];
-        __syncthreads();
-        // backward: u = (S_t x S_s x S_r) w
-        if (lane_on)                               // r-direction: point a
-#pragma unroll
-            for (int c = 0; c < NE; ++c) {
-                VT acc = 0;
-                for (int aa = 0; aa < NE; ++aa) acc += Sl[0][a * NE + aa] * box[c][b][aa];
-                w2[c] = acc;
-            }
-        __syncthreads();
-        if (lane_on)
-#pragma unroll
-            for (int c = 0; c < NE; ++c) box[c][b][a] = w2[c];
-        __syncthreads();
-        if (lane_on) {                             // s-direction: point b
-#pragma unroll
-            for (int c = 0; c < NE; ++c) {
-                VT acc = 0;
-                for (int bb = 0; bb < NE; ++bb) acc += Sl[1][b * NE + bb] * box[c][bb][a];
-                w2[c] = acc;
-            }
-#pragma unroll
-            for (int c = 0; c < NE; ++c) {         // t-direction: point c, then scatter
-                VT acc = 0;
-#pragma unroll
-                for (int m = 0; m < NE; ++m) acc += Sl[2][c * NE + m] * w2[m];
-                if (idx[c] >= 0) atomicAdd(P.z + idx[c], acc);
+            for (int r = 0; r < NR; ++r) {
+                const VT lsum = lr[r] + ls;
+                in[t][r] = acc[t][r] * (lsum > cut ? gm_inverse(lsum) : VT(0));
             }
         }
 #pragma unroll
-        for (int c = 0; c < NE; ++c) idx[c] = nidx[c];
+        for (int t = 0; t < T; ++t) acc[t] = Acc{0, 0, 0, 0};
+#pragma unroll
+        for (int r = 0; r < NR; ++r)                // r backward, straight from the registers
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = A::mma(aR[r], in[t][r], acc[t]);
     }
+    put(false);                                     // lines (m_s, m_t), rows a
+    get(false);
+    contract(1, false);                             // s backward: lines (a, m_t)
+    put(true);
+    get(true);
+    // storage positions, on their way during the last contraction
+    int32_t at[T][NR];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int col = 16 * t + j, row = A::QMUL * q + A::RMUL * r;
+            at[t][r] = P.at[(row < NE ? row : 0) * C + (col < C ? col : 0)];
+        }
+    contract(2, false);                             // t backward: lines (a, b), rows c
+    VT *o = P.o + (size_t)e * BoxStore<NE>::SIZE;
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int col = 16 * t + j, row = A::QMUL * q + A::RMUL * r;
+            if (col < C && row < NE && at[t][r] >= 0) o[at[t][r]] = acc[t][r];
+        }
 }
 
 template <typename VT>
 struct CoarseParams {
-    const VT *r;              // fine residual (restrict)
-    double *b0;               // coarse right-hand side (restrict)
-    VT *y;                    // fine output z (combine)
-    const double *x0;         // coarse solution (interp)
-    const VT *zs;             // Schwarz sum (interp)
-    const double *W;          // counting weights (interp)
+    const VT *r;              // fine residual
+    double *b0;               // coarse right-hand side
     const int32_t *cmap;      // [E][8] coarse solver index or -1
     const uint8_t *owner;     // [E][n_b] 1 on the first copy of each boundary node
     const int32_t *bmap;      // [E][n_b] element-boundary map
@@ -370,13 +502,12 @@ struct CoarseParams {
     int nb;
 };
 
-// Element-based forms (one 64-lane workgroup per element, N1 known at
-// compile time so that each lane's points are unrolled and their loads are
-// in flight together).  Every unique node is handled by exactly one local
-// copy: element-interior points and, on element boundaries, the copy that
-// comes first in the node's copy list (owner flag, built on the host).
-//
-// Restriction: b0[corner c of e] += sum over owned points of phi_c(x) r[g].
+// Restriction on its own (the coarse part without the local solves): one
+// 64-lane workgroup per element, N1 known at compile time so that each lane's
+// points are unrolled and their loads are in flight together.  Every unique
+// node is handled by exactly one local copy: element-interior points and, on
+// element boundaries, the copy that comes first in the node's copy list
+// (owner flag, built on the host).  b0[corner c of e] += sum over owned points of phi_c(x) r[g].
 template <int N1, typename VT>
 __global__ void __launch_bounds__(64) k_restrict_e(CoarseParams<VT> P) {
     constexpr int N = N1 - 1, NP = N1 * N1 * N1, Q = (NP + 63) / 64;
@@ -424,46 +555,224 @@ __global__ void __launch_bounds__(64) k_restrict_e(CoarseParams<VT> P) {
         }
 }
 
-// z[g] = W[g] zs[g] + (P x0)[g] at the owned points of each element (0 on
-// Dirichlet nodes); the element's coarse corner values are loaded once.
-template <int N1, typename VT>
-__global__ void __launch_bounds__(64) k_combine_e(CoarseParams<VT> P) {
-    constexpr int N = N1 - 1, NP = N1 * N1 * N1, Q = (NP + 63) / 64;
-    const int64_t e = blockIdx.x;
+// Sum of the overlapping local solutions and the coarse correction:
+//   z[g] = (sum of the box values that map to g) / (their number) + (P x0)[g],
+// 0 on Dirichlet nodes, in a fixed order.  The local solves leave each box
+// whole (o); adding them with atomics instead cost 0.7 ms at 48^3 (99 million,
+// resolved beyond the L2s), a cleared vector and 0.27 ms of combination.
+// 0.41 ms there for 1.6 GB (counted): the scattered list loads set the pace
+// (every extension value loaded at its interior point, six mostly idle loads
+// per point: 0.54 ms).
+// One element per wave; it sums
+//   * its interior nodes: the element's own value and, on the layer next to a
+//     face with a neighbour, the value of the neighbour's extension plane, at a
+//     position that is linear in the face coordinates (NbrFace): no index list;
+//   * the boundary nodes that appear in it first (a contiguous range of the
+//     solver order): a list of storage positions built at bind time (k_sum_count,
+//     k_sum_fill, k_sum_sort), the element's own copy in front, which also
+//     places the node for P.
+// I: 32-bit positions while they fit, 64-bit ones above.
+struct NbrFace {
+    int32_t e;                // neighbour across the face or -1
+    int32_t base, sp, sq;     // its storage position of face point (p, q): base + p sp + q sq
+};
+
+template <typename VT, typename I>
+struct SumParams {
+    const VT *o;              // [E][BoxStore::SIZE] local solutions, or null (no local part)
+    VT *z;
+    const double *x0;         // coarse solution, or null (no coarse part)
+    const int32_t *cmap;      // [E][8] coarse index of each element corner or -1
+    const double *xi;         // GLL nodes [N+1]
+    const NbrFace *nbr;       // [E][6]
+    const I *off, *pos;       // lists of the boundary nodes
+    const int32_t *bpos2l;    // local index of an element's boundary point
+    const int32_t *first;     // [E + 1] first boundary node that an element owns
+    int64_t E, n_bnd;
+};
+
+template <int NE, typename VT, typename I>
+__global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT, I> P) {
+    using St = BoxStore<NE>;
+    constexpr int N = St::N, N1 = St::N1, NM = N - 1, NI = St::NI, NF = NM * NM;
+    constexpr int QI = (NI + 63) / 64, QF = (NF + 63) / 64, W = kGmBlock / 64;
+    constexpr int64_t B = St::SIZE;
+    __shared__ double phi[2][N1];                     // shape functions at the nodes
+    __shared__ uint16_t b2l[St::NB];
+    __shared__ double zs[W][NI];                      // interior sums of the wave's element
+    for (int x = threadIdx.x; x < St::NB; x += kGmBlock) b2l[x] = (uint16_t)P.bpos2l[x];
+    if (threadIdx.x < N1) {
+        const double x = P.xi[threadIdx.x];
+        phi[0][threadIdx.x] = 0.5 * (1.0 - x);
+        phi[1][threadIdx.x] = 0.5 * (1.0 + x);
+    }
+    __syncthreads();
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t e = (int64_t)blockIdx.x * W + wv;
+    if (e >= P.E) return;
+    const int32_t g0 = P.first[e], g1 = P.first[e + 1];
+    int32_t nbe[6];
+#pragma unroll
+    for (int f = 0; f < 6; ++f) nbe[f] = P.nbr[e * 6 + f].e;
+    // interior points: the element's own values, then every face's layer of
+    // the neighbour's extension plane, one lane per face point
+    double *zb = zs[wv];
+    if (P.o) {
+        VT own[QI], ext[6][QF];
+#pragma unroll
+        for (int u = 0; u < QI; ++u) own[u] = P.o[e * B + min(lane + 64 * u, NI - 1)];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            const NbrFace nf = P.nbr[e * 6 + f];
+#pragma unroll
+            for (int u = 0; u < QF; ++u) {
+                const int t = min(lane + 64 * u, NF - 1), p = t % NM + 1, q = t / NM + 1;
+                ext[f][u] = P.o[nf.e >= 0 ? (int64_t)nf.e * B + nf.base + p * nf.sp + q * nf.sq : e * B];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < QI; ++u)
+            if (lane + 64 * u < NI) zb[lane + 64 * u] = (double)own[u];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            if (nbe[f] < 0) continue;
+            constexpr int s[3] = {1, NM, NM * NM};
+            const int d = f / 2, sp = s[d == 0 ? 1 : 0], sq = s[d == 2 ? 1 : 2];
+#pragma unroll
+            for (int u = 0; u < QF; ++u) {
+                const int t = lane + 64 * u;
+                if (t < NF) zb[(f % 2 ? (NM - 1) * s[d] : 0) + t % NM * sp + t / NM * sq] += (double)ext[f][u];
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
     double xc[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         const int32_t gc = P.cmap[e * 8 + c];
         xc[c] = (P.x0 && gc >= 0) ? P.x0[gc] : 0.0;
     }
+    auto coarse = [&](int i, int j, int k) {
+        double r[4];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int l = threadIdx.x + 64 * q;
-        if (l < NP) {
-            const int i = l % N1, j = (l / N1) % N1, k = l / (N1 * N1);
-            const bool bnd = i == 0 || i == N || j == 0 || j == N || k == 0 || k == N;
-            int64_t g;
-            bool own, dir = false;
-            if (bnd) {
-                const int b = gm_bpos(i, j, k, N1);
-                const int32_t m = P.bmap[e * P.nb + b];
-                own = P.owner[e * P.nb + b];
-                dir = m < 0;
-                g = m & 0x7fffffff;
-            } else {
-                g = gm_interior(P.n_bnd, e, i, j, k, N);
-                own = true;
-            }
-            if (own) {
-                const double wi[2] = {0.5 * (1.0 - P.xi[i]), 0.5 * (1.0 + P.xi[i])};
-                const double wj[2] = {0.5 * (1.0 - P.xi[j]), 0.5 * (1.0 + P.xi[j])};
-                const double wk[2] = {0.5 * (1.0 - P.xi[k]), 0.5 * (1.0 + P.xi[k])};
-                double zc = 0.0;
+        for (int c = 0; c < 4; ++c) r[c] = phi[0][i] * xc[2 * c] + phi[1][i] * xc[2 * c + 1];
+        return phi[0][k] * (phi[0][j] * r[0] + phi[1][j] * r[1]) +
+               phi[1][k] * (phi[0][j] * r[2] + phi[1][j] * r[3]);
+    };
+    // boundary nodes: two per lane and pass, the first four positions of their
+    // lists requested together (a pass waits for off, pos and the values in turn)
+    constexpr int U = 2, V = 4;
+    for (int32_t ga = g0 + lane; ga < g1; ga += 64 * U) {
+        I lo[U], hi[U], own[U];
+        I at[U][V];
+        double sum[U];
 #pragma unroll
-                for (int c = 0; c < 8; ++c) zc += wi[c & 1] * wj[(c >> 1) & 1] * wk[(c >> 2) & 1] * xc[c];
-                const double zsv = P.zs ? P.W[g] * (double)P.zs[g] : 0.0;
-                P.y[g] = (VT)(dir ? 0.0 : zsv + zc);
+        for (int u = 0; u < U; ++u) {
+            const int32_t g = ga + 64 * u < g1 ? ga + 64 * u : ga;
+            lo[u] = P.off[g];
+            hi[u] = P.off[g + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int t = 0; t < V; ++t)
+                at[u][t] = lo[u] < hi[u] ? P.pos[lo[u] + t < hi[u] ? lo[u] + t : lo[u]] : (I)0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            own[u] = at[u][0];
+            sum[u] = 0.0;
+            if (P.o) {
+                VT v[V];
+#pragma unroll
+                for (int t = 0; t < V; ++t) v[t] = P.o[at[u][t]];
+#pragma unroll
+                for (int t = 0; t < V; ++t)
+                    if (lo[u] + t < hi[u]) sum[u] += (double)v[t];
             }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (ga + 64 * u >= g1) break;
+            double z = 0.0;
+            if (lo[u] < hi[u]) {                      // else a Dirichlet node: 0
+                if (P.o) {
+                    for (I t = lo[u] + V; t < hi[u]; ++t) sum[u] += (double)P.o[P.pos[t]];
+                    z = sum[u] * (1.0 / (double)(hi[u] - lo[u]));
+                }
+                if (P.x0) {
+                    const int l = b2l[(int)(own[u] - (I)e * (I)B) - NI];
+                    z += coarse(l % N1, l / N1 % N1, l / St::F2);
+                }
+            }
+            P.z[ga + 64 * u] = (VT)z;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < QI; ++u) {
+        const int l = lane + 64 * u;
+        if (l >= NI) break;
+        const int x[3] = {l % NM + 1, (l / NM) % NM + 1, l / (NM * NM) + 1};
+        double z = 0.0;
+        if (P.o) {
+            int cnt = 1;
+#pragma unroll
+            for (int f = 0; f < 6; ++f) cnt += x[f / 2] == (f % 2 ? N - 1 : 1) && nbe[f] >= 0;
+            z = zb[l] * (1.0 / cnt);
+        }
+        if (P.x0) z += coarse(x[0], x[1], x[2]);
+        P.z[P.n_bnd + e * NI + l] = (VT)z;
+    }
+}
+
+// Lists of the storage positions of every boundary node: counts, then
+// positions (in any order), then each list in ascending order with its first
+// element point in front.  `cur` starts at zero for both.
+template <int NE>
+__global__ void __launch_bounds__(kGmBlock) k_sum_count(int64_t npoints, int64_t n_bnd,
+                                                        const int32_t *__restrict__ fmap,
+                                                        uint32_t *__restrict__ cur) {
+    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < npoints;
+         x += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t g = fmap[x];
+        if (g >= 0 && g < n_bnd) atomicAdd(cur + g, 1u);
+    }
+}
+
+template <int NE, typename I>
+__global__ void __launch_bounds__(kGmBlock) k_sum_fill(int64_t npoints, int64_t n_bnd,
+                                                       const int32_t *__restrict__ fmap,
+                                                       const int32_t *__restrict__ at,
+                                                       const I *__restrict__ off,
+                                                       uint32_t *__restrict__ cur,
+                                                       I *__restrict__ pos) {
+    constexpr int B = NE * NE * NE;
+    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < npoints;
+         x += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t g = fmap[x];
+        if (g >= 0 && g < n_bnd)
+            pos[off[g] + atomicAdd(cur + g, 1u)] = (I)(x / B) * (I)BoxStore<NE>::SIZE + (I)at[x % B];
+    }
+}
+
+template <int NE, typename I>
+__global__ void __launch_bounds__(kGmBlock) k_sum_sort(int64_t n_bnd, const I *__restrict__ off,
+                                                       I *__restrict__ pos) {
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= n_bnd) return;
+    const I lo = off[g], hi = off[g + 1];
+    for (I t = lo + 1; t < hi; ++t) {
+        const I x = pos[t];
+        I u = t;
+        for (; u > lo && pos[u - 1] > x; --u) pos[u] = pos[u - 1];
+        pos[u] = x;
+    }
+    for (I t = lo; t < hi; ++t) {
+        const I x = pos[t];
+        if ((int)(x % (I)BoxStore<NE>::SIZE) < BoxStore<NE>::NI + BoxStore<NE>::NB) {
+            for (I u = t; u > lo; --u) pos[u] = pos[u - 1];
+            pos[lo] = x;
+            break;
         }
     }
 }
@@ -886,21 +1195,26 @@ struct sem_gmres_s {
     std::vector<double> S, lam;      // [E][3][NE][NE], [E][3][NE]
     std::vector<int32_t> ghost;      // [E][6][(N+1)^2]
     std::vector<int32_t> cmap;       // [E][8]
-    std::vector<double> W;           // [n_u]
+    std::vector<NbrFace> nbr;        // [E][6]
     std::vector<uint8_t> owner;      // [E][n_b] first copy of each boundary node
     // device
     char *ws = nullptr;
     size_t ws_bytes = 0;
     size_t coarse_ws = 0;
     CoarsePlan cplan;                // assembled coarse operator and its solve
-    double *dS = nullptr, *dlam = nullptr, *dW = nullptr, *dxi = nullptr;
+    double *dS = nullptr, *dlam = nullptr, *dxi = nullptr;
     float *dS32 = nullptr, *dlam32 = nullptr;   // FP32 copies (reduced precisions only)
     int32_t *dghost = nullptr, *dcmap = nullptr;
     uint8_t *downer = nullptr;
     int32_t *dfmap = nullptr;
     uint16_t *down = nullptr;
-    int fdm_per_cu[2] = {0, 0};      // resident FDM workgroups per CU (FP64, FP32)
-    double *zs = nullptr, *b0 = nullptr, *x0 = nullptr;
+    NbrFace *dnbr = nullptr;
+    void *doff = nullptr, *dpos = nullptr;   // storage positions of the boundary nodes
+    int32_t *dat = nullptr;          // storage positions of a box
+    int32_t *dfirst = nullptr;       // [E + 1] first boundary node that an element owns
+    std::vector<int32_t> first;
+    double *o = nullptr;             // local solutions (FP32 ones use the first half)
+    double *b0 = nullptr, *x0 = nullptr;
     double *V = nullptr, *Z = nullptr, *w = nullptr, *r = nullptr;
     double *part = nullptr, *coef = nullptr;
     float *rhs32 = nullptr, *d32 = nullptr;
@@ -926,7 +1240,7 @@ static int face_corner(int f, int p, int q) {
 
 // Host set-up of the local solves: face neighbours and their orientation
 // from the corner (vertex) ids, the extension maps, element lengths, 1D
-// operators and their generalised eigendecompositions, counting weights.
+// operators and their generalised eigendecompositions.
 static sem_status build_local(sem_gmres G) {
     sem_ctx c = G->ctx;
     const int N = c->N, n1 = N + 1, NE = N + 3, F2 = n1 * n1;
@@ -993,6 +1307,7 @@ static sem_status build_local(sem_gmres G) {
         return c->n_bnd + e * (int64_t)(nm * nm * nm) + ((k - 1) * nm + (j - 1)) * nm + (i - 1);
     };
     std::vector<double> lens_nb(E * 6, -1.0);
+    G->nbr.assign(E * 6, NbrFace{-1, 0, 0, 0});
     for (int64_t e = 0; e < E; ++e)
         for (int f = 0; f < 6; ++f) {
             const int64_t n = nbr[e * 6 + f];
@@ -1019,6 +1334,14 @@ static sem_status build_local(sem_gmres G) {
             if (ax < 0) return gfail(G, SEM_ERR_MESH, "degenerate face orientation");
             const int inward = loc[0][ax] == 0 ? 1 : -1;
             lens_nb[e * 6 + f] = L[n * 3 + ax];
+            // the neighbour's extension plane over this face (BoxStore)
+            NbrFace &nf = G->nbr[e * 6 + f];
+            nf.e = (int32_t)n;
+            nf.base = c->np + (2 * ax + (inward == 1 ? 0 : 1)) * F2;
+            const int d1 = ax == 0 ? 1 : 0, d2 = ax == 2 ? 1 : 2;
+            nf.base += loc[0][d1] + n1 * loc[0][d2];
+            nf.sp = dP[d1] + n1 * dP[d2];
+            nf.sq = dQ[d1] + n1 * dQ[d2];
             for (int q = 0; q < n1; ++q)
                 for (int p = 0; p < n1; ++p) {
                     int x[3];
@@ -1028,22 +1351,6 @@ static sem_status build_local(sem_gmres G) {
                     G->ghost[(e * 6 + f) * F2 + p + n1 * q] = (int32_t)g;
                 }
         }
-    // counting weights: element nodes plus mapped extension points
-    std::vector<double> cnt(c->n_unique, 0.0);
-    for (int64_t e = 0; e < E; ++e) {
-        for (int k = 0; k <= N; ++k)
-            for (int j = 0; j <= N; ++j)
-                for (int i = 0; i <= N; ++i) {
-                    const int64_t g = node_of(e, i, j, k);
-                    if (g >= 0) cnt[g] += 1.0;
-                }
-        for (int q = 0; q < 6 * F2; ++q) {
-            const int32_t g = G->ghost[e * 6 * F2 + q];
-            if (g >= 0) cnt[g] += 1.0;
-        }
-    }
-    G->W.assign(c->n_unique, 0.0);
-    for (int64_t g = 0; g < c->n_unique; ++g) G->W[g] = cnt[g] > 0 ? 1.0 / cnt[g] : 0.0;
     // 1D operators and eigendecompositions
     std::vector<double> Khat((size_t)n1 * n1, 0.0);
     for (int i = 0; i < n1; ++i)
@@ -1150,7 +1457,15 @@ extern "C" sem_status sem_gmres_create(sem_ctx c, int restart, sem_gmres *out) {
     }
     // the first copy of every element-boundary node owns it
     G->owner.assign((size_t)c->E * c->nb, 0);
-    for (int64_t g = 0; g < c->n_bnd; ++g) G->owner[c->csr_idx[c->csr_off[g]]] = 1;
+    // (boundary nodes are numbered by first appearance, so an element owns a
+    // contiguous range of them)
+    G->first.assign((size_t)c->E + 1, 0);
+    for (int64_t g = 0; g < c->n_bnd; ++g) {
+        const int32_t own = c->csr_idx[c->csr_off[g]];
+        G->owner[own] = 1;
+        G->first[own / c->nb + 1] += 1;
+    }
+    for (int64_t e = 0; e < c->E; ++e) G->first[e + 1] += G->first[e];
     // coarse index of every element corner (Dirichlet: -1)
     G->cmap.assign(c->E * 8, -1);
     for (int64_t e = 0; e < c->E; ++e)
@@ -1171,6 +1486,15 @@ extern "C" void sem_gmres_free(sem_gmres G) {
 
 extern "C" const char *sem_gmres_last_error(sem_gmres G) { return G ? G->err.c_str() : ""; }
 
+// BoxStore::SIZE at run time, and whether its positions exceed 32 bits.
+static int64_t box_size(sem_gmres G) {
+    const int n1 = G->ctx->n1;
+    return (n1 * n1 * n1 + 6 * n1 * n1 + 15) / 16 * 16;
+}
+static bool wide_positions(sem_gmres G) {
+    return (uint64_t)G->ctx->E * box_size(G) > UINT32_MAX;
+}
+
 static size_t gm_layout(sem_gmres G, size_t *off) {
     sem_ctx c = G->ctx;
     const int64_t E = c->E, NE = G->NE, n1 = c->n1;
@@ -1185,9 +1509,9 @@ static size_t gm_layout(sem_gmres G, size_t *off) {
     off[2] = take(8 * (size_t)E * 3 * NE);            // lambda
     off[3] = take(4 * (size_t)E * 6 * n1 * n1);       // ghost map
     off[4] = take(4 * (size_t)E * 8);                 // coarse map
-    off[5] = take(8 * (size_t)c->n_unique);           // W
+    off[5] = take(sizeof(NbrFace) * (size_t)E * 6);   // neighbour faces
     off[6] = take(8 * 16);                            // xi
-    off[7] = take(8 * (size_t)c->n_unique);           // zs
+    off[7] = take(8 * (size_t)E * box_size(G));       // local solutions
     off[8] = take(8 * (size_t)G->coarse->n_unique);   // b0
     off[9] = take(8 * (size_t)G->coarse->n_unique);   // x0
     off[10] = take(8 * (size_t)G->ld * (G->m + 1));   // V
@@ -1206,20 +1530,56 @@ static size_t gm_layout(sem_gmres G, size_t *off) {
     off[21] = take(low ? 4 * (size_t)E * 3 * NE * NE : 0);
     off[22] = take(low ? 4 * (size_t)E * 3 * NE : 0);
     off[23] = take(coarse_bytes(G->cplan));
+    // position lists of the boundary nodes: at most every element-boundary
+    // point and the rim of every extension plane
+    const size_t is = wide_positions(G) ? 8 : 4;
+    off[24] = take(is * ((size_t)c->n_bnd + 1));
+    off[25] = take(is * (size_t)E * (c->nb + 6 * 4 * c->N));
+    off[26] = take(4 * (size_t)NE * NE * NE);         // storage positions of a box
+    off[27] = take(4 * ((size_t)E + 1));              // first owned boundary node
     return o;
 }
 
 extern "C" sem_status sem_gmres_workspace_size(sem_gmres G, size_t *bytes) {
     if (!G || !bytes) return gfail(G, SEM_ERR_INVALID, "null argument");
-    size_t off[24];
+    size_t off[28];
     *bytes = gm_layout(G, off);
     return SEM_OK;
+}
+
+// Position lists of the boundary nodes from the box gather maps (the counts
+// are summed on the host; the local solutions' array holds them meanwhile).
+template <int NE, typename I>
+static hipError_t build_positions(sem_gmres G, hipStream_t s) {
+    sem_ctx c = G->ctx;
+    const int64_t nb = c->n_bnd, np = c->E * NE * NE * NE;
+    uint32_t *cur = reinterpret_cast<uint32_t *>(G->o);
+    I *off = static_cast<I *>(G->doff), *pos = static_cast<I *>(G->dpos);
+    const dim3 gp(gm_grid(np)), gn((unsigned)((nb + kGmBlock - 1) / kGmBlock)), t(kGmBlock);
+    std::vector<uint32_t> cnt(nb);
+    std::vector<I> hoff(nb + 1);
+    hipError_t e = launch_fill32(reinterpret_cast<float *>(cur), nb, 0.0f, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_sum_count<NE>, gp, t, 0, s, np, nb, (const int32_t *)G->dfmap, cur);
+    e = hipMemcpyAsync(cnt.data(), cur, 4 * (size_t)nb, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    hoff[0] = 0;
+    for (int64_t g = 0; g < nb; ++g) hoff[g + 1] = hoff[g] + cnt[g];
+    e = hipMemcpyAsync(off, hoff.data(), sizeof(I) * hoff.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = launch_fill32(reinterpret_cast<float *>(cur), nb, 0.0f, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_sum_fill<NE, I>), gp, t, 0, s, np, nb, (const int32_t *)G->dfmap,
+                       (const int32_t *)G->dat, (const I *)off, cur, pos);
+    hipLaunchKernelGGL((k_sum_sort<NE, I>), gn, t, 0, s, nb, (const I *)off, pos);
+    e = hipGetLastError();
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;   // hoff is a temporary
 }
 
 extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t bytes,
                                                sem_stream stream) {
     if (!G || !dev) return gfail(G, SEM_ERR_INVALID, "null argument");
-    size_t off[24];
+    size_t off[28];
     const size_t need = gm_layout(G, off);
     if (bytes < need)
         return gfail(G, SEM_ERR_OOM, "workspace of " + std::to_string(bytes) + " bytes, need " +
@@ -1239,9 +1599,14 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
     G->dlam = reinterpret_cast<double *>(w + off[2]);
     G->dghost = reinterpret_cast<int32_t *>(w + off[3]);
     G->dcmap = reinterpret_cast<int32_t *>(w + off[4]);
-    G->dW = reinterpret_cast<double *>(w + off[5]);
+    G->dnbr = reinterpret_cast<NbrFace *>(w + off[5]);
     G->dxi = reinterpret_cast<double *>(w + off[6]);
-    G->zs = reinterpret_cast<double *>(w + off[7]);
+    G->o = reinterpret_cast<double *>(w + off[7]);
+    G->doff = w + off[24];
+    G->dpos = w + off[25];
+    G->dat = reinterpret_cast<int32_t *>(w + off[26]);
+    G->dfirst = reinterpret_cast<int32_t *>(w + off[27]);
+    SEM_HIP(c, hipMemcpyAsync(G->dfirst, G->first.data(), 4 * G->first.size(), hipMemcpyHostToDevice, s));
     G->b0 = reinterpret_cast<double *>(w + off[8]);
     G->x0 = reinterpret_cast<double *>(w + off[9]);
     G->V = reinterpret_cast<double *>(w + off[10]);
@@ -1271,7 +1636,8 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
     }
     SEM_HIP(c, hipMemcpyAsync(G->dghost, G->ghost.data(), 4 * G->ghost.size(), hipMemcpyHostToDevice, s));
     SEM_HIP(c, hipMemcpyAsync(G->dcmap, G->cmap.data(), 4 * G->cmap.size(), hipMemcpyHostToDevice, s));
-    SEM_HIP(c, hipMemcpyAsync(G->dW, G->W.data(), 8 * G->W.size(), hipMemcpyHostToDevice, s));
+    SEM_HIP(c, hipMemcpyAsync(G->dnbr, G->nbr.data(), sizeof(NbrFace) * G->nbr.size(),
+                              hipMemcpyHostToDevice, s));
     SEM_HIP(c, hipMemcpyAsync(G->downer, G->owner.data(), G->owner.size(), hipMemcpyHostToDevice, s));
     SEM_HIP(c, hipMemcpyAsync(G->dxi, c->xi, 8 * c->n1, hipMemcpyHostToDevice, s));
     // box gather maps from the element and face maps
@@ -1279,7 +1645,7 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
     case ne:                                                                                    \
         hipLaunchKernelGGL(k_fdm_map<ne>, dim3((unsigned)c->E), dim3(((ne) * (ne) + 63) / 64 * 64), 0, \
                            s, (const int32_t *)G->dghost, dptr<int32_t>(c, c->L.bmap),        \
-                           (const uint8_t *)G->downer, c->E, c->n_bnd, c->nb, G->dfmap, G->down); \
+                           (const uint8_t *)G->downer, c->E, c->n_bnd, c->nb, G->dfmap, G->down, G->dat); \
         break;
     switch (G->NE) {
         SEM_FMAP(5) SEM_FMAP(6) SEM_FMAP(7) SEM_FMAP(8) SEM_FMAP(9) SEM_FMAP(10) SEM_FMAP(11)
@@ -1288,7 +1654,41 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
     }
 #undef SEM_FMAP
     SEM_HIP(c, hipGetLastError());
+    hipError_t pe = hipErrorInvalidValue;
+#define SEM_POS(ne)                                                                              \
+    case ne: pe = wide_positions(G) ? build_positions<ne, uint64_t>(G, s)                        \
+                                    : build_positions<ne, uint32_t>(G, s);                       \
+        break;
+    switch (G->NE) {
+        SEM_POS(5) SEM_POS(6) SEM_POS(7) SEM_POS(8) SEM_POS(9) SEM_POS(10) SEM_POS(11) SEM_POS(12)
+        SEM_POS(13) SEM_POS(14) SEM_POS(15) SEM_POS(16)
+        default: break;
+    }
+#undef SEM_POS
+    SEM_HIP(c, pe);
     SEM_HIP(c, hipStreamSynchronize(s));
+    return SEM_OK;
+}
+
+// z from the local solutions (o null: without them) and the coarse solution.
+template <typename VT, typename I>
+static sem_status combine(sem_gmres G, const VT *o, bool coarse, VT *z, hipStream_t s) {
+    sem_ctx c = G->ctx;
+    SumParams<VT, I> P{o, z, coarse ? G->x0 : nullptr, G->dcmap, G->dxi, G->dnbr,
+                       static_cast<const I *>(G->doff), static_cast<const I *>(G->dpos),
+                       dptr<int32_t>(c, c->L.bpos2l), G->dfirst, c->E, c->n_bnd};
+    const dim3 g((unsigned)((c->E + kGmBlock / 64 - 1) / (kGmBlock / 64))), t(kGmBlock);
+#define SEM_SUM(ne)                                                       \
+    case ne:                                                              \
+        hipLaunchKernelGGL((k_fdm_sum<ne, VT, I>), g, t, 0, s, P);        \
+        break;
+    switch (G->NE) {
+        SEM_SUM(5) SEM_SUM(6) SEM_SUM(7) SEM_SUM(8) SEM_SUM(9) SEM_SUM(10) SEM_SUM(11) SEM_SUM(12)
+        SEM_SUM(13) SEM_SUM(14) SEM_SUM(15) SEM_SUM(16)
+        default: return gfail(G, SEM_ERR_UNSUPPORTED, "order");
+    }
+#undef SEM_SUM
+    SEM_HIP(c, hipGetLastError());
     return SEM_OK;
 }
 
@@ -1303,9 +1703,9 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
     // with both parts the coarse restriction is summed in the local-solve
     // kernel's gather (the residual is read once)
     const bool fused = local && coarse;
-    // the Schwarz sum in the vectors' precision (an FP32 sum uses the first
-    // half of the FP64 buffer)
-    VT *zs = reinterpret_cast<VT *>(G->zs);
+    // the local solutions in the vectors' precision (FP32 ones use the first
+    // half of the FP64 array)
+    VT *o = reinterpret_cast<VT *>(G->o);
     constexpr bool f32 = std::is_same<VT, float>::value;
     if (local) {
         const VT *S, *lam;
@@ -1313,31 +1713,16 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
             if (!G->dS32) return gfail(G, SEM_ERR_STATE, "no FP32 tables: no reduced precision at set-up");
             S = G->dS32;
             lam = G->dlam32;
-            SEM_HIP(c, launch_fill32(zs, n, 0.0f, s));
         } else {
             S = G->dS;
             lam = G->dlam;
-            SEM_HIP(c, launch_fill(zs, n, 0.0, s));
         }
-        FdmParams<VT> P{r,       zs, S, lam, G->dfmap, c->E,
+        FdmParams<VT> P{r,       o, G->dat, S, lam, G->dfmap, c->E,
                         G->down, fused ? G->b0 : nullptr, G->dcmap, G->dxi};
-        // persistent: the workgroups resident at once, each taking every
-        // grid-th element
 #define SEM_FDM(ne)                                                                          \
-    case ne: {                                                                               \
-        const int nt = ((ne) * (ne) + 63) / 64 * 64;                                         \
-        int &per_cu = G->fdm_per_cu[f32 ? 1 : 0];                                            \
-        if (per_cu == 0) {                                                                   \
-            int nb = 0;                                                                      \
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fdm<ne, VT>, nt, 0) !=   \
-                    hipSuccess || nb < 1)                                                    \
-                nb = 1;                                                                      \
-            per_cu = nb;                                                                     \
-        }                                                                                    \
-        const int64_t grid = std::min<int64_t>(c->E, (int64_t)per_cu * c->num_cus);         \
-        hipLaunchKernelGGL((k_fdm<ne, VT>), dim3((unsigned)grid), dim3(nt), 0, s, P);        \
-        break;                                                                               \
-    }
+    case ne:                                                                                 \
+        hipLaunchKernelGGL((k_fdm<ne, VT>), dim3((unsigned)c->E), dim3(64), 0, s, P);        \
+        break;
         switch (G->NE) {
             SEM_FDM(5) SEM_FDM(6) SEM_FDM(7) SEM_FDM(8) SEM_FDM(9) SEM_FDM(10) SEM_FDM(11)
             SEM_FDM(12) SEM_FDM(13) SEM_FDM(14) SEM_FDM(15) SEM_FDM(16)
@@ -1346,9 +1731,9 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
 #undef SEM_FDM
         SEM_HIP(c, hipGetLastError());
     }
-    CoarseParams<VT> C{r,       G->b0,   z,     G->x0, local ? zs : nullptr, G->dW, G->dcmap,
-                       G->downer, dptr<int32_t>(c, c->L.bmap), G->dxi, c->E, c->n_bnd, c->nb};
     if (coarse) {
+        CoarseParams<VT> C{r,       G->b0, G->dcmap, G->downer, dptr<int32_t>(c, c->L.bmap), G->dxi,
+                           c->E, c->n_bnd, c->nb};
 #define SEM_RESTRICT(n1)                                                                    \
     case n1:                                                                                \
         hipLaunchKernelGGL((k_restrict_e<n1, VT>), dim3((unsigned)c->E), dim3(64), 0, s, C); \
@@ -1364,21 +1749,9 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
         // 10 Jacobi-PCG iterations from zero on the coarse operator (which
         // leave b0 cleared for the next application)
         SEM_HIP(c, coarse_solve(G->cplan, s));
-    } else {
-        C.x0 = nullptr;
     }
-#define SEM_COMBINE(n1)                                                                     \
-    case n1:                                                                                \
-        hipLaunchKernelGGL((k_combine_e<n1, VT>), dim3((unsigned)c->E), dim3(64), 0, s, C); \
-        break;
-    switch (c->n1) {
-        SEM_COMBINE(3) SEM_COMBINE(4) SEM_COMBINE(5) SEM_COMBINE(6) SEM_COMBINE(7) SEM_COMBINE(8)
-        SEM_COMBINE(9) SEM_COMBINE(10) SEM_COMBINE(11) SEM_COMBINE(12) SEM_COMBINE(13) SEM_COMBINE(14)
-        default: return gfail(G, SEM_ERR_UNSUPPORTED, "order");
-    }
-#undef SEM_COMBINE
-    SEM_HIP(c, hipGetLastError());
-    return SEM_OK;
+    return wide_positions(G) ? combine<VT, uint64_t>(G, local ? o : nullptr, coarse, z, s)
+                             : combine<VT, uint32_t>(G, local ? o : nullptr, coarse, z, s);
 }
 
 extern "C" sem_status sem_gmres_precondition(sem_gmres G, const double *r, double *z,

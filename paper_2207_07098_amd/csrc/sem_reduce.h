@@ -27,4 +27,12 @@ __device__ __forceinline__ double wave_sum63(double v) {
     return v;
 }
 
+// The same sum for every lane.
+__device__ __forceinline__ double wave_total(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, wave_sum63(v));
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, 63);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), 63);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 }  // namespace sem

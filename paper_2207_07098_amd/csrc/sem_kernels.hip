@@ -31,12 +31,26 @@
 #include <mutex>
 
 #include "sem_internal.h"
+#include "sem_reduce.h"
 
 namespace sem {
 
 namespace {
 
 constexpr int kVecBlock = 512;
+// Fused CG iterations (see k_cg_update): bytes of the CG vectors (r, p, w, x,
+// dinv) and operator partials up to which they are used, and their grid (one
+// resident set of workgroups: 256 CUs x 4).
+// The vectors' limit is where they stop staying in the 256 MB Infinity Cache.
+// PCG per iteration at N = 7, separate launches -> fused: FP64 12^3 37.1 ->
+// 29.7 us, 16^3 64.3 -> 54.7, 24^3 (193 MB) 159.7 -> 151.6, 28^3 (305 MB) 240 ->
+// 233, but 32^3 (456 MB) 350 -> 353 and 48^3 1159 -> 1222; FP32 32^3 (228 MB) 206
+// -> 198, but 40^3 (444 MB) 369 -> 390.  16384 partials are the most that a
+// measured fused mesh had.  Grids of 512 and 2048 workgroups: 152.7 and 157.9 us
+// at 24^3 in FP64.
+constexpr int64_t kCachedVectors = (int64_t)320 << 20;
+constexpr int kFusedPartials = 16384;
+constexpr unsigned kFusedGrid = 1024;
 
 struct bf16_t {
     uint16_t v;
@@ -1074,7 +1088,7 @@ template <int N1, typename GS>
 hipError_t ax_dispatch_n(sem_ctx c, const void *Gp, const float *gscale, const void *Dp,
                          const void *DTp, const void *u, void *y, int in_local, int out_mode,
                          double *partials, CgState *st, const AxTile &t, hipStream_t s,
-                         bool vec64) {
+                         bool vec64, int *fuse) {
     using T = typename GT<GS>::T;
     constexpr int C = N1 * N1;
     constexpr size_t BUF = (size_t)N1 * N1 * (N1 + 1);
@@ -1171,16 +1185,19 @@ hipError_t ax_dispatch_n(sem_ctx c, const void *Gp, const float *gscale, const v
         SEM_AXL(MODE_ATOMIC, T, N1, false);
     }
 #undef SEM_AXL
-    if (partials)
+    // up to *fuse partials are left to the next kernel, which is told their number
+    const bool leave = fuse && grid <= *fuse;
+    if (partials && !leave)
         hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, (int)FIN_AX,
                            (const double *)partials, (int)grid, st);
+    if (fuse) *fuse = leave ? (int)grid : 0;
     return hipGetLastError();
 }
 
 template <typename GS>
 hipError_t ax_dispatch(sem_ctx c, int prec, const void *u, void *y, int in_local, int out_mode,
                        double *partials, CgState *st, const AxTile &t, hipStream_t s,
-                       bool vec64) {
+                       bool vec64, int *fuse) {
     const void *G = c->ws + c->L.G[prec];
     const float *gsc = dptr<float>(c, c->L.gscale[prec]);
     const bool f64 = prec == SEM_FP64;
@@ -1189,7 +1206,7 @@ hipError_t ax_dispatch(sem_ctx c, int prec, const void *u, void *y, int in_local
 #define SEM_AXN(n)                                                                         \
     case n:                                                                                \
         return ax_dispatch_n<n, GS>(c, G, gsc, D, DT, u, y, in_local, out_mode, partials, st, \
-                                    t, s, vec64);
+                                    t, s, vec64, fuse);
     switch (c->n1) {
         SEM_AXN(2) SEM_AXN(3) SEM_AXN(4) SEM_AXN(5) SEM_AXN(6) SEM_AXN(7) SEM_AXN(8)
         SEM_AXN(9) SEM_AXN(10) SEM_AXN(11) SEM_AXN(12) SEM_AXN(13) SEM_AXN(14)
@@ -1481,86 +1498,195 @@ struct Vec<float> {
     static constexpr int W = 4;
 };
 
-// x += alpha p; r -= alpha w; reduces r.r and r.z (z = dinv r); updates beta
-// and the convergence state.  16-byte accesses; n % W entries in a tail.
 // Streaming accesses of the vector kernels (each vector is touched once per
-// kernel); SEM_VEC_NT selects non-temporal hints.
-#ifndef SEM_VEC_NT
-#define SEM_VEC_NT 1
-#endif
-template <typename V>
+// kernel): with a non-temporal hint unless the solver's vectors stay in the
+// Infinity Cache from one kernel to the next (FP64 PCG at 24^3, N = 7 with the
+// hint 174.5, without 168.7 us per iteration; 32^3 356.7 and 376.9 us).
+template <bool NT, typename V>
 __device__ __forceinline__ V vld(const V *p) {
-    if (SEM_VEC_NT) return __builtin_nontemporal_load(p);
+    if (NT) return __builtin_nontemporal_load(p);
     return *p;
 }
-template <typename V>
+template <bool NT, typename V>
 __device__ __forceinline__ void vst(V v, V *p) {
-    if (SEM_VEC_NT) __builtin_nontemporal_store(v, p);
+    if (NT) __builtin_nontemporal_store(v, p);
     else *p = v;
 }
 
+// Sums of NV values over a workgroup of whole waves, in a fixed order; every
+// thread gets them.  One barrier; another must lie between two sums through
+// the same `red`.
+template <int NV>
+__device__ __forceinline__ void vec_block_sum(double (&v)[NV], double (*red)[kVecBlock / 64]) {
+    const int wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int a = 0; a < NV; ++a) v[a] = wave_sum63(v[a]);
+    if ((threadIdx.x & 63) == 63)
+#pragma unroll
+        for (int a = 0; a < NV; ++a) red[a][wv] = v[a];
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < NV; ++a) {
+        double s = red[a][0];
+#pragma unroll
+        for (int q = 1; q < kVecBlock / 64; ++q) s += red[a][q];
+        v[a] = s;
+    }
+}
+
+// This thread's share of the packed partials of nblocks workgroups.
+template <int NV>
+__device__ __forceinline__ void load_partials(const double *__restrict__ part, int nblocks,
+                                              double (&v)[NV]) {
+#pragma unroll
+    for (int a = 0; a < NV; ++a) v[a] = 0.0;
+    for (int q = threadIdx.x; q < nblocks; q += kVecBlock)
+#pragma unroll
+        for (int a = 0; a < NV; ++a) v[a] += part[(size_t)q * NV + a];
+}
+
+// FUSED: the reductions of a CG iteration without launches of their own.  Every
+// workgroup of the vector kernel sums the preceding kernel's nin partials
+// itself and takes the scalar step on its copy of the state `in`; workgroup 0
+// leaves the new state in `out`, which only the next kernel reads.  The first
+// vectors of the workgroup are requested before the sum.  A k_finish launch
+// between two kernels costs 4 to 6 us and a gap, two per iteration: 4^3, N = 5
+// 20.8 -> 13.6 us per iteration, 11^3, N = 8 45.1 -> 37.8 us; larger meshes and
+// the limit at kCachedVectors.
+
 // r -= alpha w and the reductions r.r, r.z (z = dinv r) for beta.  The
 // matching x += alpha p is left to k_cg_p, which reads the old p anyway, so
-// p is read once per iteration.
-template <typename T>
-__global__ void k_cg_update(int64_t n, T *__restrict__ r, const T *__restrict__ w,
-                            const T *__restrict__ dinv, double *partials, CgState *st) {
-    if (st->done) return;
+// p is read once per iteration.  16-byte accesses; n % W entries in a tail.
+template <typename T, bool FUSED>
+__global__ void __launch_bounds__(kVecBlock)
+k_cg_update(int64_t n, T *__restrict__ r, const T *__restrict__ w, const T *__restrict__ dinv,
+            double *partials, const CgState *in, CgState *out, const double *pin, int nin) {
     using V = typename Vec<T>::type;
     constexpr int W = Vec<T>::W;
-    const T alpha = (T)st->alpha;
-    double rr = 0, rz = 0;
-    const int64_t nv = n / W, stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr bool NT = !FUSED;
+    __shared__ double red[2][kVecBlock / 64];
+    __shared__ CgState sh;
+    const int64_t nv = n / W, stride = (int64_t)gridDim.x * kVecBlock;
+    const int64_t t0 = (int64_t)blockIdx.x * kVecBlock + threadIdx.x;
+    const int stopped = in->done | in->pause;
+    V rv = V(0), wv = V(0), dv = V(0);
+    if (!stopped && t0 < nv) {
+        rv = vld<NT>(reinterpret_cast<V *>(r) + t0);
+        wv = vld<NT>(reinterpret_cast<const V *>(w) + t0);
+        dv = vld<NT>(reinterpret_cast<const V *>(dinv) + t0);
+    }
+    T alpha;
+    if (FUSED) {
+        double t[1] = {0.0};
+        if (!stopped) {
+            load_partials<1>(pin, nin, t);
+            vec_block_sum<1>(t, red);
+        }
+        if (threadIdx.x == 0) {
+            sh = *in;
+            sh.xstep = 0;                     // the previous iteration's x step has run
+            if (!sh.done && sh.pause) sh.done = 2;
+            else if (!sh.done) cg_finish_ax(sh, t[0]);
+            if (blockIdx.x == 0) *out = sh;
+        }
+        __syncthreads();
+        if (sh.done) return;
+        alpha = (T)sh.alpha;
+    } else {
+        if (in->done) return;
+        alpha = (T)in->alpha;
+    }
+    double s[2] = {0.0, 0.0};
     for (int64_t v = t0; v < nv; v += stride) {
-        V rv = vld(reinterpret_cast<V *>(r) + v);
-        const V wv = vld(reinterpret_cast<const V *>(w) + v);
-        const V dv = vld(reinterpret_cast<const V *>(dinv) + v);
+        if (v != t0) {
+            rv = vld<NT>(reinterpret_cast<V *>(r) + v);
+            wv = vld<NT>(reinterpret_cast<const V *>(w) + v);
+            dv = vld<NT>(reinterpret_cast<const V *>(dinv) + v);
+        }
         rv -= alpha * wv;
-        vst(rv, reinterpret_cast<V *>(r) + v);
+        vst<NT>(rv, reinterpret_cast<V *>(r) + v);
 #pragma unroll
         for (int c = 0; c < W; ++c) {
-            rr += (double)rv[c] * (double)rv[c];
-            rz += (double)rv[c] * (double)(dv[c] * rv[c]);
+            s[0] += (double)rv[c] * (double)rv[c];
+            s[1] += (double)rv[c] * (double)(dv[c] * rv[c]);
         }
     }
     for (int64_t q = nv * W + t0; q < n; q += stride) {
         const T rq = r[q] - alpha * w[q];
         r[q] = rq;
-        rr += (double)rq * (double)rq;
-        rz += (double)rq * (double)(dinv[q] * rq);
+        s[0] += (double)rq * (double)rq;
+        s[1] += (double)rq * (double)(dinv[q] * rq);
     }
-    double v2[2] = {rr, rz};
-    block_partial<2>(v2, partials);
+    __syncthreads();                          // red: the first sum has been read
+    vec_block_sum<2>(s, red);
+    if (threadIdx.x == 0) {
+        partials[(size_t)blockIdx.x * 2] = s[0];
+        partials[(size_t)blockIdx.x * 2 + 1] = s[1];
+    }
 }
 
 // x += alpha p with the old p (owed by this iteration's residual update),
 // then, unless the CG has stopped, p = dinv r + beta p and w = 0 on boundary
 // nodes for the next operator.  A stopped CG keeps its p (a residual
 // replacement may continue along it).
-template <typename T>
-__global__ void k_cg_p(int64_t n, int64_t n_bnd, const T *__restrict__ r, T *__restrict__ p,
-                       T *__restrict__ w, const T *__restrict__ dinv, T *__restrict__ x,
-                       const CgState *st) {
-    if (!st->xstep) return;                   // no update ran in this iteration
-    const bool dir = !st->done;
+template <typename T, bool FUSED>
+__global__ void __launch_bounds__(kVecBlock)
+k_cg_p(int64_t n, int64_t n_bnd, const T *__restrict__ r, T *__restrict__ p, T *__restrict__ w,
+       const T *__restrict__ dinv, T *__restrict__ x, const CgState *in, CgState *out,
+       const double *pin, int nin) {
     using V = typename Vec<T>::type;
     constexpr int W = Vec<T>::W;
-    const T alpha = (T)st->alpha, beta = (T)st->beta;
-    const int64_t nv = n / W, stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr bool NT = !FUSED;
+    __shared__ double red[2][kVecBlock / 64];
+    __shared__ CgState sh;
+    const int64_t nv = n / W, stride = (int64_t)gridDim.x * kVecBlock;
+    const int64_t t0 = (int64_t)blockIdx.x * kVecBlock + threadIdx.x;
     const int64_t nbv = n_bnd / W;            // whole vectors inside the boundary block
+    // FUSED: `in` is the update's state (its step is still to be taken)
+    const bool idle = FUSED ? in->done != 0 : in->xstep == 0;   // no update ran
+    V rv = V(0), dv = V(0), pv = V(0), xv = V(0);
+    if (!idle && t0 < nv) {
+        rv = vld<NT>(reinterpret_cast<const V *>(r) + t0);
+        dv = vld<NT>(reinterpret_cast<const V *>(dinv) + t0);
+        pv = vld<NT>(reinterpret_cast<V *>(p) + t0);
+        xv = vld<NT>(reinterpret_cast<V *>(x) + t0);
+    }
+    T alpha, beta;
+    bool dir;
+    if (FUSED) {
+        double t[2] = {0.0, 0.0};
+        if (!idle) {
+            load_partials<2>(pin, nin, t);
+            vec_block_sum<2>(t, red);
+        }
+        if (threadIdx.x == 0) {
+            sh = *in;
+            if (!sh.done) cg_finish_update(sh, t[0], t[1]);
+            if (blockIdx.x == 0) *out = sh;
+        }
+        __syncthreads();
+        alpha = (T)sh.alpha;
+        beta = (T)sh.beta;
+        dir = !sh.done;
+    } else {
+        alpha = (T)in->alpha;
+        beta = (T)in->beta;
+        dir = !in->done;
+    }
+    if (idle) return;
     if (dir) {
         for (int64_t v = t0; v < nv; v += stride) {
-            const V rv = vld(reinterpret_cast<const V *>(r) + v);
-            const V dv = vld(reinterpret_cast<const V *>(dinv) + v);
-            V pv = vld(reinterpret_cast<V *>(p) + v);
-            V xv = vld(reinterpret_cast<V *>(x) + v);
+            if (v != t0) {
+                rv = vld<NT>(reinterpret_cast<const V *>(r) + v);
+                dv = vld<NT>(reinterpret_cast<const V *>(dinv) + v);
+                pv = vld<NT>(reinterpret_cast<V *>(p) + v);
+                xv = vld<NT>(reinterpret_cast<V *>(x) + v);
+            }
             xv += alpha * pv;
             pv = dv * rv + beta * pv;
-            vst(xv, reinterpret_cast<V *>(x) + v);
-            vst(pv, reinterpret_cast<V *>(p) + v);
-            if (v < nbv) vst(V(0), reinterpret_cast<V *>(w) + v);
+            vst<NT>(xv, reinterpret_cast<V *>(x) + v);
+            vst<NT>(pv, reinterpret_cast<V *>(p) + v);
+            if (v < nbv) vst<NT>(V(0), reinterpret_cast<V *>(w) + v);
         }
         for (int64_t q = nbv * W + t0; q < n_bnd; q += stride) w[q] = 0;
         for (int64_t q = nv * W + t0; q < n; q += stride) {
@@ -1569,10 +1695,12 @@ __global__ void k_cg_p(int64_t n, int64_t n_bnd, const T *__restrict__ r, T *__r
         }
     } else {
         for (int64_t v = t0; v < nv; v += stride) {
-            const V pv = vld(reinterpret_cast<const V *>(p) + v);
-            V xv = vld(reinterpret_cast<V *>(x) + v);
+            if (v != t0) {
+                pv = vld<NT>(reinterpret_cast<const V *>(p) + v);
+                xv = vld<NT>(reinterpret_cast<V *>(x) + v);
+            }
             xv += alpha * pv;
-            vst(xv, reinterpret_cast<V *>(x) + v);
+            vst<NT>(xv, reinterpret_cast<V *>(x) + v);
         }
         for (int64_t q = nv * W + t0; q < n; q += stride) x[q] += alpha * p[q];
     }
@@ -1753,11 +1881,11 @@ __global__ void __launch_bounds__(256) k_vec_batch(BatchArgs A, int mode) {
                     // at even nodes), the odd last node of a problem separately
                     const int64_t ve = it.end >> 1;
                     for (int64_t v = (it.begin >> 1) + threadIdx.x; v < ve; v += blockDim.x) {
-                        d2v rv = vld(reinterpret_cast<const d2v *>(r) + v);
-                        const d2v wq = vld(reinterpret_cast<const d2v *>(wv) + v);
-                        const d2v dv = vld(reinterpret_cast<const d2v *>(dinv) + v);
+                        d2v rv = vld<true>(reinterpret_cast<const d2v *>(r) + v);
+                        const d2v wq = vld<true>(reinterpret_cast<const d2v *>(wv) + v);
+                        const d2v dv = vld<true>(reinterpret_cast<const d2v *>(dinv) + v);
                         rv -= alpha * wq;
-                        vst(rv, reinterpret_cast<d2v *>(r) + v);
+                        vst<true>(rv, reinterpret_cast<d2v *>(r) + v);
                         s0 += rv.x * rv.x + rv.y * rv.y;
                         s1 += rv.x * (dv.x * rv.x) + rv.y * (dv.y * rv.y);
                     }
@@ -1771,15 +1899,15 @@ __global__ void __launch_bounds__(256) k_vec_batch(BatchArgs A, int mode) {
                 } else if (mode == 2 && dir) {
                     const int64_t ve = it.end >> 1, nb = pb.n_bnd;
                     for (int64_t v = (it.begin >> 1) + threadIdx.x; v < ve; v += blockDim.x) {
-                        const d2v rv = vld(reinterpret_cast<const d2v *>(r) + v);
-                        const d2v dv = vld(reinterpret_cast<const d2v *>(dinv) + v);
-                        d2v pv = vld(reinterpret_cast<const d2v *>(p) + v);
-                        d2v xv = vld(reinterpret_cast<const d2v *>(x) + v);
+                        const d2v rv = vld<true>(reinterpret_cast<const d2v *>(r) + v);
+                        const d2v dv = vld<true>(reinterpret_cast<const d2v *>(dinv) + v);
+                        d2v pv = vld<true>(reinterpret_cast<const d2v *>(p) + v);
+                        d2v xv = vld<true>(reinterpret_cast<const d2v *>(x) + v);
                         xv += alpha * pv;
                         pv = dv * rv + beta * pv;
-                        vst(xv, reinterpret_cast<d2v *>(x) + v);
-                        vst(pv, reinterpret_cast<d2v *>(p) + v);
-                        if (2 * v + 1 < nb) vst(d2v{0.0, 0.0}, reinterpret_cast<d2v *>(wv) + v);
+                        vst<true>(xv, reinterpret_cast<d2v *>(x) + v);
+                        vst<true>(pv, reinterpret_cast<d2v *>(p) + v);
+                        if (2 * v + 1 < nb) vst<true>(d2v{0.0, 0.0}, reinterpret_cast<d2v *>(wv) + v);
                         else if (2 * v < nb) wv[2 * v] = 0.0;
                     }
                     if ((it.end & 1) && threadIdx.x == 0) {
@@ -2024,16 +2152,17 @@ hipError_t launch_rhs(sem_ctx c, const double *fL, const double *f, double *b, h
 }
 
 hipError_t launch_ax(sem_ctx c, int prec, const void *u, void *y, int in_local, int out_mode,
-                     double *partials, CgState *st, const AxTile &t, hipStream_t s, bool vec64) {
+                     double *partials, CgState *st, const AxTile &t, hipStream_t s, bool vec64,
+                     int *fuse) {
     switch (prec) {
         case SEM_FP64:
-            return ax_dispatch<double>(c, prec, u, y, in_local, out_mode, partials, st, t, s, vec64);
+            return ax_dispatch<double>(c, prec, u, y, in_local, out_mode, partials, st, t, s, vec64, fuse);
         case SEM_FP32:
-            return ax_dispatch<float>(c, prec, u, y, in_local, out_mode, partials, st, t, s, vec64);
+            return ax_dispatch<float>(c, prec, u, y, in_local, out_mode, partials, st, t, s, vec64, fuse);
         case SEM_FP16_SCALED:
-            return ax_dispatch<_Float16>(c, prec, u, y, in_local, out_mode, partials, st, t, s, vec64);
+            return ax_dispatch<_Float16>(c, prec, u, y, in_local, out_mode, partials, st, t, s, vec64, fuse);
         case SEM_BF16_SCALED:
-            return ax_dispatch<bf16_t>(c, prec, u, y, in_local, out_mode, partials, st, t, s, vec64);
+            return ax_dispatch<bf16_t>(c, prec, u, y, in_local, out_mode, partials, st, t, s, vec64, fuse);
         default: return hipErrorInvalidValue;
     }
 }
@@ -2139,40 +2268,55 @@ hipError_t launch_cg_begin(sem_ctx c, int level, const void *b, void *x, void *r
     return hipGetLastError();
 }
 
+// Residual update and direction update of one iteration; nax > 0: the
+// operator's partials are still to be summed, else k_finish has run.
+template <typename T>
+static void launch_cg_vectors(sem_ctx c, T *x, T *r, T *p, T *w, const T *dinv, CgState *st, int nax,
+                              hipStream_t s) {
+    const int64_t n = c->n_unique;
+    const double *pax = partials_site(c, 0);
+    double *pup = partials_site(c, 2);
+    if (nax > 0) {
+        const unsigned g = std::min(vec_grid(n / Vec<T>::W), kFusedGrid);
+        CgState *mid = state_ptr(c) + 3;      // the update's state (no solver level's)
+        hipLaunchKernelGGL((k_cg_update<T, true>), dim3(g), dim3(kVecBlock), 0, s, n, r, (const T *)w,
+                           dinv, pup, (const CgState *)st, mid, pax, nax);
+        hipLaunchKernelGGL((k_cg_p<T, true>), dim3(g), dim3(kVecBlock), 0, s, n, c->n_bnd,
+                           (const T *)r, p, w, dinv, x, (const CgState *)mid, st,
+                           (const double *)pup, (int)g);
+        return;
+    }
+    const unsigned g = vec_grid(n);
+    hipLaunchKernelGGL((k_cg_update<T, false>), dim3(g), dim3(kVecBlock), 0, s, n, r, (const T *)w,
+                       dinv, pup, (const CgState *)st, st, pax, 0);
+    hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, (int)FIN_UPDATE, (const double *)pup,
+                       (int)g, st);
+    hipLaunchKernelGGL((k_cg_p<T, false>), dim3(g), dim3(kVecBlock), 0, s, n, c->n_bnd, (const T *)r,
+                       p, w, dinv, x, (const CgState *)st, st, (const double *)pup, 0);
+}
+
 hipError_t launch_cg_iteration(sem_ctx c, int level, int prec, void *x, void *r, void *p, void *w,
                                CgState *st, int deterministic, hipStream_t s) {
     const Layout &L = c->L;
-    const int64_t n = c->n_unique;
     hipError_t e;
     const bool vec64 = level == 0;     // level 0: FP64 vectors (any operator precision)
+    int fuse = 5 * c->n_unique * (vec64 ? 8 : 4) <= kCachedVectors ? kFusedPartials : 0;
     if (deterministic && (prec == SEM_FP64 || !vec64)) {
-        e = launch_ax(c, prec, p, w, 0, OUT_COMPACT, partials_site(c, 0), st, c->tile[prec], s);
+        e = launch_ax(c, prec, p, w, 0, OUT_COMPACT, partials_site(c, 0), st, c->tile[prec], s, false,
+                      &fuse);
         if (e != hipSuccess) return e;
         e = launch_gather_sum(c, prec, c->ws + L.wb, w, s);
     } else {
         e = launch_ax(c, prec, p, w, 0, OUT_ATOMIC, partials_site(c, 0), st, c->tile[prec], s,
-                      vec64);
+                      vec64, &fuse);
     }
     if (e != hipSuccess) return e;
-    if (vec64) {
-        hipLaunchKernelGGL(k_cg_update<double>, dim3(vec_grid(n)), dim3(kVecBlock), 0, s, n,
-                           (double *)r, (const double *)w, dptr<double>(c, L.dinv64),
-                           partials_site(c, 2), st);
-        hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, (int)FIN_UPDATE,
-                           (const double *)partials_site(c, 2), (int)vec_grid(n), st);
-        hipLaunchKernelGGL(k_cg_p<double>, dim3(vec_grid(n)), dim3(kVecBlock), 0, s, n, c->n_bnd,
-                           (const double *)r, (double *)p, (double *)w, dptr<double>(c, L.dinv64),
-                           (double *)x, (const CgState *)st);
-    } else {
-        hipLaunchKernelGGL(k_cg_update<float>, dim3(vec_grid(n)), dim3(kVecBlock), 0, s, n,
-                           (float *)r, (const float *)w, dptr<float>(c, L.dinv32),
-                           partials_site(c, 2), st);
-        hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, (int)FIN_UPDATE,
-                           (const double *)partials_site(c, 2), (int)vec_grid(n), st);
-        hipLaunchKernelGGL(k_cg_p<float>, dim3(vec_grid(n)), dim3(kVecBlock), 0, s, n, c->n_bnd,
-                           (const float *)r, (float *)p, (float *)w, dptr<float>(c, L.dinv32),
-                           (float *)x, (const CgState *)st);
-    }
+    if (vec64)
+        launch_cg_vectors<double>(c, (double *)x, (double *)r, (double *)p, (double *)w,
+                                  dptr<double>(c, L.dinv64), st, fuse, s);
+    else
+        launch_cg_vectors<float>(c, (float *)x, (float *)r, (float *)p, (float *)w,
+                                 dptr<float>(c, L.dinv32), st, fuse, s);
     return hipGetLastError();
 }
 

@@ -196,7 +196,7 @@ struct BatchProb {               // device-resident, one per problem
     double unscale;              // 1 / scale
     int outer_done;              // refinement finished (or handed to FP64)
     int pad_;
-    CgState *st;
+    CgState *st, *st2;           // st2: after the update of a fused iteration
     int64_t E, n_bnd, n_u;
     int n1, epb;
     int ax_begin, ax_end;        // operator work items of this problem
@@ -217,6 +217,8 @@ struct BatchLaunch {             // host-side description of one batch launch
     int n_ax, n_vec, nprob;
     double *ax_partials, *vec_partials;
     int ax_grid, vec_grid, max_n1;
+    int64_t n_total;             // nodes of all problems
+    int max_partials;            // most partials of one problem's reduction
     int ax_lo[sem::kMaxN1 + 1], ax_hi[sem::kMaxN1 + 1];   // operator items of each order
     int threads[sem::kMaxN1 + 1], grid_cap[sem::kMaxN1 + 1];  // operator tile of each order
 };

@@ -1516,8 +1516,8 @@ __device__ __forceinline__ void vst(V v, V *p) {
 // Sums of NV values over a workgroup of whole waves, in a fixed order; every
 // thread gets them.  One barrier; another must lie between two sums through
 // the same `red`.
-template <int NV>
-__device__ __forceinline__ void vec_block_sum(double (&v)[NV], double (*red)[kVecBlock / 64]) {
+template <int NV, int B = kVecBlock>
+__device__ __forceinline__ void wg_sum(double (&v)[NV], double (*red)[B / 64]) {
     const int wv = threadIdx.x >> 6;
 #pragma unroll
     for (int a = 0; a < NV; ++a) v[a] = wave_sum63(v[a]);
@@ -1529,7 +1529,7 @@ __device__ __forceinline__ void vec_block_sum(double (&v)[NV], double (*red)[kVe
     for (int a = 0; a < NV; ++a) {
         double s = red[a][0];
 #pragma unroll
-        for (int q = 1; q < kVecBlock / 64; ++q) s += red[a][q];
+        for (int q = 1; q < B / 64; ++q) s += red[a][q];
         v[a] = s;
     }
 }
@@ -1580,7 +1580,7 @@ k_cg_update(int64_t n, T *__restrict__ r, const T *__restrict__ w, const T *__re
         double t[1] = {0.0};
         if (!stopped) {
             load_partials<1>(pin, nin, t);
-            vec_block_sum<1>(t, red);
+            wg_sum<1>(t, red);
         }
         if (threadIdx.x == 0) {
             sh = *in;
@@ -1618,7 +1618,7 @@ k_cg_update(int64_t n, T *__restrict__ r, const T *__restrict__ w, const T *__re
         s[1] += (double)rq * (double)(dinv[q] * rq);
     }
     __syncthreads();                          // red: the first sum has been read
-    vec_block_sum<2>(s, red);
+    wg_sum<2>(s, red);
     if (threadIdx.x == 0) {
         partials[(size_t)blockIdx.x * 2] = s[0];
         partials[(size_t)blockIdx.x * 2 + 1] = s[1];
@@ -1657,7 +1657,7 @@ k_cg_p(int64_t n, int64_t n_bnd, const T *__restrict__ r, T *__restrict__ p, T *
         double t[2] = {0.0, 0.0};
         if (!idle) {
             load_partials<2>(pin, nin, t);
-            vec_block_sum<2>(t, red);
+            wg_sum<2>(t, red);
         }
         if (threadIdx.x == 0) {
             sh = *in;
@@ -1764,7 +1764,7 @@ struct BatchArgs {
     const BatchAxItem *ax_items;
     const BatchVecItem *vec_items;
     int n_ax, n_vec;
-    double *ax_partials;     // [n_ax][4]
+    double *ax_partials;     // [n_ax]
     double *vec_partials;    // [n_vec][4]
     int phase;               // operator: 0 FP64 CG (p -> w), 1 FP32 inner CG
                              // (p32 -> w32), 2 FP64 residual (x -> w)
@@ -1835,121 +1835,170 @@ k_ax_batch(BatchArgs A, int lo, int hi) {
         if (!skip) batch_group<N1, T>(A, pb, it.group, lds, dot);
         __shared__ double red[16];
         const double sdot = block_sum(dot, red);
-        if (threadIdx.x == 0) A.ax_partials[(size_t)w * 4] = sdot;
+        if (threadIdx.x == 0) A.ax_partials[w] = sdot;
         __syncthreads();                 // LDS is rewritten by the next item
     }
 }
 
-// mode 0: begin (x = 0, r = b, p = dinv r, w_bnd = 0; partials r.z, r.r, b.b)
-// mode 1: update (x += alpha p, r -= alpha w; partials r.r, r.z)
-// mode 2: p = dinv r + beta p, w_bnd = 0 (no partials)
-// T = double: the problem's FP64 CG vectors; T = float: the FP32 inner
-// vectors of the refinement (sums in FP64 either way).
+// The vectors of a problem: T = double its FP64 CG, T = float the FP32 inner
+// CG of the refinement (sums in FP64 either way).
 template <typename T>
-__global__ void __launch_bounds__(256) k_vec_batch(BatchArgs A, int mode) {
+struct BatchVecs {
+    T *x, *r, *p, *w;
+    const T *b, *dinv;
+    __device__ __forceinline__ BatchVecs(const BatchProb &pb) {
+        if constexpr (std::is_same<T, double>::value) {
+            x = pb.x; r = pb.r; p = pb.p; w = pb.w; b = pb.b; dinv = pb.dinv;
+        } else {
+            x = pb.x32; r = pb.r32; p = pb.p32; w = pb.w32; b = pb.b32; dinv = pb.dinv32;
+        }
+    }
+};
+
+// x = 0, r = b, p = dinv r, w_bnd = 0; partials r.z, r.r, b.b.
+template <typename T>
+__global__ void __launch_bounds__(256) k_begin_batch(BatchArgs A) {
     for (int w = blockIdx.x; w < A.n_vec; w += gridDim.x) {
         const BatchVecItem it = A.vec_items[w];
         const BatchProb &pb = A.probs[it.prob];
-        double s0 = 0, s1 = 0, s2 = 0;
-        // mode 1: r -= alpha w (x is left to mode 2); mode 2: x += alpha p
-        // with the old p when the update ran, then p and w unless stopped
-        const bool skip = (A.phase == 1 && pb.outer_done) ||
-                          (mode == 1 && pb.st->done) || (mode == 2 && !pb.st->xstep);
-        const bool dir = !pb.st->done;
-        if (!skip) {
-            T *x, *r, *p, *wv;
-            const T *b, *dinv;
-            if constexpr (std::is_same<T, double>::value) {
-                x = pb.x; r = pb.r; p = pb.p; wv = pb.w; b = pb.b; dinv = pb.dinv;
-            } else {
-                x = pb.x32; r = pb.r32; p = pb.p32; wv = pb.w32; b = pb.b32; dinv = pb.dinv32;
-            }
-            const double alpha = pb.st->alpha, beta = pb.st->beta;
-            for (int64_t q = it.begin + threadIdx.x; mode == 0 && q < it.end; q += blockDim.x) {
-                const T bq = b[q], zq = dinv[q] * bq;
-                x[q] = T(0);
-                r[q] = bq;
-                p[q] = zq;
-                if (q < pb.n_bnd) wv[q] = T(0);
+        double s0 = 0, s1 = 0;
+        if (!(A.phase == 1 && pb.outer_done)) {
+            const BatchVecs<T> v(pb);
+            for (int64_t q = it.begin + threadIdx.x; q < it.end; q += blockDim.x) {
+                const T bq = v.b[q], zq = v.dinv[q] * bq;
+                v.x[q] = T(0);
+                v.r[q] = bq;
+                v.p[q] = zq;
+                if (q < pb.n_bnd) v.w[q] = T(0);
                 s0 += (double)bq * (double)zq;
                 s1 += (double)bq * (double)bq;
-                s2 += (double)bq * (double)bq;
-            }
-            if constexpr (std::is_same<T, double>::value) {
-                if (mode == 1) {
-                    // 16-byte streaming accesses over whole pairs (items start
-                    // at even nodes), the odd last node of a problem separately
-                    const int64_t ve = it.end >> 1;
-                    for (int64_t v = (it.begin >> 1) + threadIdx.x; v < ve; v += blockDim.x) {
-                        d2v rv = vld<true>(reinterpret_cast<const d2v *>(r) + v);
-                        const d2v wq = vld<true>(reinterpret_cast<const d2v *>(wv) + v);
-                        const d2v dv = vld<true>(reinterpret_cast<const d2v *>(dinv) + v);
-                        rv -= alpha * wq;
-                        vst<true>(rv, reinterpret_cast<d2v *>(r) + v);
-                        s0 += rv.x * rv.x + rv.y * rv.y;
-                        s1 += rv.x * (dv.x * rv.x) + rv.y * (dv.y * rv.y);
-                    }
-                    if ((it.end & 1) && threadIdx.x == 0) {
-                        const int64_t q = it.end - 1;
-                        const double rq = r[q] - alpha * wv[q];
-                        r[q] = rq;
-                        s0 += rq * rq;
-                        s1 += rq * (dinv[q] * rq);
-                    }
-                } else if (mode == 2 && dir) {
-                    const int64_t ve = it.end >> 1, nb = pb.n_bnd;
-                    for (int64_t v = (it.begin >> 1) + threadIdx.x; v < ve; v += blockDim.x) {
-                        const d2v rv = vld<true>(reinterpret_cast<const d2v *>(r) + v);
-                        const d2v dv = vld<true>(reinterpret_cast<const d2v *>(dinv) + v);
-                        d2v pv = vld<true>(reinterpret_cast<const d2v *>(p) + v);
-                        d2v xv = vld<true>(reinterpret_cast<const d2v *>(x) + v);
-                        xv += alpha * pv;
-                        pv = dv * rv + beta * pv;
-                        vst<true>(xv, reinterpret_cast<d2v *>(x) + v);
-                        vst<true>(pv, reinterpret_cast<d2v *>(p) + v);
-                        if (2 * v + 1 < nb) vst<true>(d2v{0.0, 0.0}, reinterpret_cast<d2v *>(wv) + v);
-                        else if (2 * v < nb) wv[2 * v] = 0.0;
-                    }
-                    if ((it.end & 1) && threadIdx.x == 0) {
-                        const int64_t q = it.end - 1;
-                        x[q] += alpha * p[q];
-                        p[q] = dinv[q] * r[q] + beta * p[q];
-                        if (q < nb) wv[q] = 0.0;
-                    }
-                } else if (mode == 2) {
-                    for (int64_t q = it.begin + threadIdx.x; q < it.end; q += blockDim.x)
-                        x[q] += alpha * p[q];
-                }
-            } else {
-                const T af = (T)alpha, bf = (T)beta;
-                if (mode == 1) {
-                    for (int64_t q = it.begin + threadIdx.x; q < it.end; q += blockDim.x) {
-                        const T rq = r[q] - af * wv[q];
-                        r[q] = rq;
-                        s0 += (double)rq * (double)rq;
-                        s1 += (double)rq * (double)(dinv[q] * rq);
-                    }
-                } else if (mode == 2) {
-                    for (int64_t q = it.begin + threadIdx.x; q < it.end; q += blockDim.x) {
-                        const T pq = p[q];
-                        x[q] += af * pq;
-                        if (dir) {
-                            p[q] = dinv[q] * r[q] + bf * pq;
-                            if (q < pb.n_bnd) wv[q] = T(0);
-                        }
-                    }
-                }
             }
         }
-        if (mode != 2) {
-            __shared__ double red[16];
-            const double a0 = block_sum(s0, red), a1 = block_sum(s1, red), a2 = block_sum(s2, red);
+        __shared__ double red[16];
+        const double a0 = block_sum(s0, red), a1 = block_sum(s1, red);
+        if (threadIdx.x == 0) {
+            A.vec_partials[(size_t)w * 4 + 0] = a0;
+            A.vec_partials[(size_t)w * 4 + 1] = a1;
+            A.vec_partials[(size_t)w * 4 + 2] = a1;
+        }
+    }
+}
+
+// The two vector passes of an iteration over all problems, as k_cg_update
+// (DIR = false: r -= alpha w; partials r.r, r.z) and k_cg_p (DIR = true: x +=
+// alpha p with the old p when the update ran, then p and w_bnd unless the
+// problem has stopped).  16-byte accesses; items start at multiples of 512
+// nodes.  FUSED: every item sums its problem's partials of the pass before and
+// takes the scalar step on its copy of the state; the problem's first item
+// leaves it in the other slot (st: before the update, st2: after it), and the
+// vectors, small enough to stay in the Infinity Cache, go without
+// non-temporal hints.
+// Bounded by the vectors' traffic.  32 problems of 5.3 M nodes together: items
+// of 16384 nodes, of which 324 left the chip idle, took 36 us a pass and
+// k_finish_batch 4.6 us and a gap.
+template <typename T, bool DIR, bool FUSED>
+__global__ void __launch_bounds__(256) k_vec_batch(BatchArgs A) {
+    using V = typename Vec<T>::type;
+    constexpr int W = Vec<T>::W;
+    constexpr bool NT = !FUSED;
+    constexpr int NW = 256 / 64;
+    __shared__ double red[2][NW];
+    __shared__ CgState sh;
+    for (int w = blockIdx.x; w < A.n_vec; w += gridDim.x) {
+        const BatchVecItem it = A.vec_items[w];
+        const BatchProb &pb = A.probs[it.prob];
+        const BatchVecs<T> v(pb);
+        const CgState *in = FUSED && DIR ? pb.st2 : pb.st;
+        // no update ran / the problem has stopped before it
+        const bool idle = DIR && !FUSED ? in->xstep == 0 : in->done != 0;
+        if (FUSED) {
+            double t[2] = {0.0, 0.0};
+            if (!idle) {
+                if (DIR) {
+                    for (int q = pb.vec_begin + threadIdx.x; q < pb.vec_end; q += 256) {
+                        t[0] += A.vec_partials[(size_t)q * 4];
+                        t[1] += A.vec_partials[(size_t)q * 4 + 1];
+                    }
+                } else {
+                    for (int q = pb.ax_begin + threadIdx.x; q < pb.ax_end; q += 256)
+                        t[0] += A.ax_partials[q];
+                }
+                wg_sum<2, 256>(t, red);
+            }
             if (threadIdx.x == 0) {
-                A.vec_partials[(size_t)w * 4 + 0] = a0;
-                A.vec_partials[(size_t)w * 4 + 1] = a1;
-                A.vec_partials[(size_t)w * 4 + 2] = a2;
+                sh = *in;
+                if (!DIR) sh.xstep = 0;       // the previous direction pass has run
+                if (!sh.done) {
+                    if (DIR) cg_finish_update(sh, t[0], t[1]);
+                    else cg_finish_ax(sh, t[0]);
+                }
+                if (w == pb.vec_begin) *(DIR ? pb.st : pb.st2) = sh;
+            }
+            __syncthreads();
+        }
+        const T alpha = (T)(FUSED ? sh.alpha : in->alpha), beta = (T)(FUSED ? sh.beta : in->beta);
+        const bool done = (FUSED ? sh.done : in->done) != 0;
+        double s[2] = {0.0, 0.0};
+        const int64_t v0 = it.begin / W + threadIdx.x, ve = it.end / W;
+        const int64_t q0 = ve * W + threadIdx.x;          // the problem's last nodes
+        if (!DIR) {
+            if (!done) {
+                for (int64_t q = v0; q < ve; q += 256) {
+                    V rv = vld<NT>(reinterpret_cast<const V *>(v.r) + q);
+                    const V wv = vld<NT>(reinterpret_cast<const V *>(v.w) + q);
+                    const V dv = vld<NT>(reinterpret_cast<const V *>(v.dinv) + q);
+                    rv -= alpha * wv;
+                    vst<NT>(rv, reinterpret_cast<V *>(v.r) + q);
+#pragma unroll
+                    for (int c = 0; c < W; ++c) {
+                        s[0] += (double)rv[c] * (double)rv[c];
+                        s[1] += (double)rv[c] * (double)(dv[c] * rv[c]);
+                    }
+                }
+                if (q0 < it.end) {
+                    const T rq = v.r[q0] - alpha * v.w[q0];
+                    v.r[q0] = rq;
+                    s[0] += (double)rq * (double)rq;
+                    s[1] += (double)rq * (double)(v.dinv[q0] * rq);
+                }
+            }
+            __syncthreads();                  // red: the first sum has been read
+            wg_sum<2, 256>(s, red);
+            if (threadIdx.x == 0) {
+                A.vec_partials[(size_t)w * 4 + 0] = s[0];
+                A.vec_partials[(size_t)w * 4 + 1] = s[1];
+            }
+        } else if (!idle) {
+            const int64_t nb = pb.n_bnd, nbv = nb / W;
+            for (int64_t q = v0; q < ve; q += 256) {
+                V pv = vld<NT>(reinterpret_cast<const V *>(v.p) + q);
+                V xv = vld<NT>(reinterpret_cast<const V *>(v.x) + q);
+                if (!done) {
+                    const V rv = vld<NT>(reinterpret_cast<const V *>(v.r) + q);
+                    const V dv = vld<NT>(reinterpret_cast<const V *>(v.dinv) + q);
+                    xv += alpha * pv;
+                    pv = dv * rv + beta * pv;
+                    vst<NT>(pv, reinterpret_cast<V *>(v.p) + q);
+                    if (q < nbv) vst<NT>(V(0), reinterpret_cast<V *>(v.w) + q);
+                    else
+#pragma unroll
+                        for (int c = 0; c < W - 1; ++c)
+                            if (q * W + c < nb) v.w[q * W + c] = T(0);
+                } else {
+                    xv += alpha * pv;
+                }
+                vst<NT>(xv, reinterpret_cast<V *>(v.x) + q);
+            }
+            if (q0 < it.end) {
+                const T pq = v.p[q0];
+                v.x[q0] += alpha * pq;
+                if (!done) {
+                    v.p[q0] = v.dinv[q0] * v.r[q0] + beta * pq;
+                    if (q0 < nb) v.w[q0] = T(0);
+                }
             }
         }
+        __syncthreads();                      // LDS is rewritten by the next item
     }
 }
 
@@ -2021,8 +2070,11 @@ __global__ void __launch_bounds__(256) k_finish_batch(BatchArgs A, int site) {
     const int lo = ax ? pb.ax_begin : pb.vec_begin, hi = ax ? pb.ax_end : pb.vec_end;
     __shared__ double red[16];
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int q = lo + threadIdx.x; q < hi; q += blockDim.x)
-        for (int a = 0; a < 3; ++a) acc[a] += part[(size_t)q * 4 + a];
+    if (ax)
+        for (int q = lo + threadIdx.x; q < hi; q += blockDim.x) acc[0] += part[q];
+    else
+        for (int q = lo + threadIdx.x; q < hi; q += blockDim.x)
+            for (int a = 0; a < 3; ++a) acc[a] += part[(size_t)q * 4 + a];
     double out[3];
     for (int a = 0; a < 3; ++a) out[a] = block_sum(acc[a], red);
     if (threadIdx.x != 0) return;
@@ -2385,7 +2437,7 @@ static void launch_batch_operator(const BatchLaunch &bl, const BatchArgs &A, hip
         const int lo = bl.ax_lo[n1], hi = bl.ax_hi[n1];
         if (hi <= lo) continue;
         const int grid = bl.grid_cap[n1] > 0 ? std::min(bl.grid_cap[n1], hi - lo) : hi - lo;
-        const size_t lds = batch_lds_bytes_n1(bl.threads[n1], n1);
+        const size_t lds = batch_lds_bytes_n1(bl.threads[n1], n1) / (sizeof(double) / sizeof(T));
         const int threads = std::max(1, bl.threads[n1] / (n1 * n1)) * n1 * n1;   // epb slots
         switch (n1) {
 #define SEM_BAXN(n)                                                                          \
@@ -2400,14 +2452,21 @@ static void launch_batch_operator(const BatchLaunch &bl, const BatchArgs &A, hip
     }
 }
 
+// Fused under the same limits as the iteration of a single mesh.
 template <typename T>
 static hipError_t batch_iteration(const BatchLaunch &bl, hipStream_t s, int phase) {
     BatchArgs A = batch_args(bl, phase);
+    const dim3 g(bl.vec_grid), t(256);
     launch_batch_operator<T>(bl, A, s);
-    hipLaunchKernelGGL(k_finish_batch, dim3(bl.nprob), dim3(256), 0, s, A, (int)FIN_AX);
-    hipLaunchKernelGGL(k_vec_batch<T>, dim3(bl.vec_grid), dim3(256), 0, s, A, 1);
-    hipLaunchKernelGGL(k_finish_batch, dim3(bl.nprob), dim3(256), 0, s, A, (int)FIN_UPDATE);
-    hipLaunchKernelGGL(k_vec_batch<T>, dim3(bl.vec_grid), dim3(256), 0, s, A, 2);
+    if (5 * bl.n_total * (int64_t)sizeof(T) <= kCachedVectors && bl.max_partials <= kFusedPartials) {
+        hipLaunchKernelGGL((k_vec_batch<T, false, true>), g, t, 0, s, A);
+        hipLaunchKernelGGL((k_vec_batch<T, true, true>), g, t, 0, s, A);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_finish_batch, dim3(bl.nprob), t, 0, s, A, (int)FIN_AX);
+    hipLaunchKernelGGL((k_vec_batch<T, false, false>), g, t, 0, s, A);
+    hipLaunchKernelGGL(k_finish_batch, dim3(bl.nprob), t, 0, s, A, (int)FIN_UPDATE);
+    hipLaunchKernelGGL((k_vec_batch<T, true, false>), g, t, 0, s, A);
     return hipGetLastError();
 }
 
@@ -2418,9 +2477,9 @@ hipError_t launch_batch_iteration(const BatchLaunch &bl, hipStream_t s, bool fp3
 hipError_t launch_batch_begin(const BatchLaunch &bl, hipStream_t s, bool fp32) {
     BatchArgs A = batch_args(bl, fp32 ? 1 : 0);
     if (fp32)
-        hipLaunchKernelGGL(k_vec_batch<float>, dim3(bl.vec_grid), dim3(256), 0, s, A, 0);
+        hipLaunchKernelGGL(k_begin_batch<float>, dim3(bl.vec_grid), dim3(256), 0, s, A);
     else
-        hipLaunchKernelGGL(k_vec_batch<double>, dim3(bl.vec_grid), dim3(256), 0, s, A, 0);
+        hipLaunchKernelGGL(k_begin_batch<double>, dim3(bl.vec_grid), dim3(256), 0, s, A);
     hipLaunchKernelGGL(k_finish_batch, dim3(bl.nprob), dim3(256), 0, s, A, (int)FIN_BEGIN);
     return hipGetLastError();
 }

@@ -53,3 +53,35 @@ def test_pcg_steps(K, N):
     r = b - op.ax(x)
     assert info["status"] == "SEM_OK" and info["fallback"] == "none", info
     assert float(r.norm() / b.norm()) <= 1.01e-9
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("meshes", [[((2, 1, 1), 2)], [((3, 2, 1), 4), ((1, 1, 1), 3), ((7, 6, 5), 7)],
+                                    [((12, 11, 10), 9), ((2, 2, 2), 5)],
+                                    [((21, 21, 21), 7)] * 3])
+def test_batch_steps(meshes):
+    """Eight batched FP64 steps against the single solves of the same
+    problems (sums in another order only, as above): one item, items of
+    several problems with odd sizes, more nodes than items of the smallest
+    size hold, and 390 MB of vectors, which take the separate reductions.
+    Then the FP32 inner iteration to a true FP64 residual of 1e-9."""
+    import paper_2207_07098_amd as sem
+    ops = [sem.Operator(F.box(K, hi=(F.meshgen.TWO_PI,) * 3, deform=0.02), N,
+                        precisions=("fp64", "fp32")) for K, N in meshes]
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rhs = [op.ax(torch.rand(op.n_unique, generator=g, dtype=torch.float64, device="cuda") - 0.5)
+           for op in ops]
+    steps = 3 if min(op.n_unique for op in ops) < 200 else 8
+    batch = sem.Batch(ops)
+    for kw in ({}, {"use_graph": False}):
+        xs, infos = batch.solve(rhs, tol=1e-14, max_iter=steps, raise_on_error=False, **kw)
+        for op, b, x, info in zip(ops, rhs, xs, infos):
+            want, one = op.solve(b, tol=1e-14, max_iter=steps, max_restart=0, raise_on_error=False)
+            assert info["iterations"] == one["iterations"], (info, one)
+            err = float((x - want).abs().max() / want.abs().max())
+            print(op.n_unique, kw, info["iterations"], "rel diff %.2e" % err, flush=True)
+            assert err <= 1e-10
+    xs, infos = batch.solve(rhs, tol=1e-9, precision="fp32")
+    for op, b, x, info in zip(ops, rhs, xs, infos):
+        assert info["status"] == "SEM_OK" and info["fallback"] == "none", info
+        assert float((b - op.ax(x)).norm() / b.norm()) <= 1.01e-9

@@ -51,11 +51,10 @@ constexpr int kGmBlock = 256;
 constexpr int kGmGrid = 2048;
 constexpr int kGmMaxVec = 32;            // basis vectors in one multi-dot
 // coef[] slots: single-vector sums at 0.., the sums of a delayed step at
-// kGmD.. (2 * kGmMaxVec + 3 values), that step's scalars at kGmScal..,
-// normalisation factor and squared norm of the new basis vector after them,
-// scalars for the update kernels at kGmMisc..
+// kGmD.. (2 * kGmMaxVec + 3 values); in the host's copy also that step's
+// scalars at kGmScal..
 constexpr int kGmD = kGmMaxVec + 2, kGmScal = kGmD + 2 * kGmMaxVec + 4;
-constexpr int kGmMisc = kGmScal + 4, kGmCoef = kGmMisc + 4;
+constexpr int kGmCoef = kGmScal + 4;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -581,6 +580,8 @@ template <typename VT, typename I>
 struct SumParams {
     const VT *o;              // [E][BoxStore::SIZE] local solutions, or null (no local part)
     VT *z;
+    VT *clear;                // cleared on the boundary nodes (the vector that the
+                              // operator adds to next), or null
     const double *x0;         // coarse solution, or null (no coarse part)
     const int32_t *cmap;      // [E][8] coarse index of each element corner or -1
     const double *xi;         // GLL nodes [N+1]
@@ -706,6 +707,7 @@ __global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT, I> P) {
                 }
             }
             P.z[ga + 64 * u] = (VT)z;
+            if (P.clear) P.clear[ga + 64 * u] = VT(0);
         }
     }
 #pragma unroll
@@ -782,7 +784,8 @@ __global__ void __launch_bounds__(kGmBlock) k_sum_sort(int64_t n_bnd, const I *_
 // values of 700 blocks, this form 4 us).
 __global__ void __launch_bounds__(kGmBlock) k_gm_finish(int nblocks,
                                                         const double *__restrict__ part,
-                                                        double *__restrict__ out) {
+                                                        double *__restrict__ out,
+                                                        double *__restrict__ host) {
     __shared__ double red[kGmBlock / 64];
     const double *p = part + (size_t)blockIdx.x * nblocks;
     double s = 0.0;
@@ -795,6 +798,7 @@ __global__ void __launch_bounds__(kGmBlock) k_gm_finish(int nblocks,
 #pragma unroll
         for (int w = 1; w < kGmBlock / 64; ++w) s += red[w];
         out[blockIdx.x] = s;
+        if (host) host[blockIdx.x] = s;       // pinned: read after an event, no copy
     }
 }
 
@@ -993,8 +997,8 @@ __device__ __forceinline__ void gm_delayed_scalars(const double *q, const double
 // once-projected one,
 //   v   = (vt - X q) / beta           (stored over vt),
 //   out = (w - X p - h v) * c          (the next slot),
-// with q, p, r, s, t from d and beta, h, c as above (block 0 stores them in
-// scal[0..2]).
+// with q, p, r, s, t from d and beta, h, c as above (block 0 stores d and
+// them for the host).
 template <int L, typename T>
 __global__ void __launch_bounds__(kGmBlock) k_gm_update2(int64_t n, int64_t ld,
                                                          const T *__restrict__ X,
@@ -1002,8 +1006,7 @@ __global__ void __launch_bounds__(kGmBlock) k_gm_update2(int64_t n, int64_t ld,
                                                          T *__restrict__ vt,
                                                          const T *__restrict__ w,
                                                          T *__restrict__ out,
-                                                         double *__restrict__ scal) {
-    using P = typename PairOf<T>::type;
+                                                         double *__restrict__ host) {
     double q[L], pv[L];
 #pragma unroll
     for (int i = 0; i < L; ++i) {
@@ -1013,10 +1016,13 @@ __global__ void __launch_bounds__(kGmBlock) k_gm_update2(int64_t n, int64_t ld,
     double beta, h, c;
     gm_delayed_scalars(q, pv, L, d[2 * L], d[2 * L + 1], d[2 * L + 2], beta, h, c);
     const double ib = beta > 0.0 ? 1.0 / beta : 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        scal[0] = beta;
-        scal[1] = h;
-        scal[2] = c;
+    if (blockIdx.x == 0) {                    // pinned host memory
+        if (threadIdx.x < 2 * L + 3) host[kGmD + threadIdx.x] = d[threadIdx.x];
+        if (threadIdx.x == 0) {
+            host[kGmScal] = beta;
+            host[kGmScal + 1] = h;
+            host[kGmScal + 2] = c;
+        }
     }
     const int64_t np = n >> 1, stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < np; p += stride) {
@@ -1054,80 +1060,58 @@ __global__ void __launch_bounds__(kGmBlock) k_gm_update2(int64_t n, int64_t ld,
     }
 }
 
-// Closing update of an Arnoldi step, normalisation included:
-// out = (v - X c) * inv, c = coef[0..L), with inv = 1/sqrt(v.v - |c|^2)
-// (the squared norm of v - X c when X is orthonormal and c = X^T v; v.v is
-// coef[L]).  Where that difference is not safely positive, inv = 1/|v|
-// instead (0 for v = 0).  Block 0 stores inv in *inv_out; part[blk] =
-// out . out, so the caller can check the normalisation.
-template <int L, typename T>
-__global__ void __launch_bounds__(kGmBlock) k_gm_orth_scale(int64_t n, int64_t ld,
-                                                            const T *__restrict__ X,
-                                                            const double *__restrict__ coef,
-                                                            const T *__restrict__ v,
-                                                            T *__restrict__ out,
-                                                            double *__restrict__ part,
-                                                            double *__restrict__ inv_out) {
+// First Arnoldi step of a cycle, from coef[0] = p = V_0 . w and coef[1] = w.w:
+// out = (w - p V_0) * c with c = 1/sqrt(w.w - p^2) (V_0 has norm one).  Where
+// that difference is not safely positive, c = 1/|w| instead (0 for w = 0).
+// Block 0 stores p, w.w and c for the host.
+template <typename T>
+__global__ void __launch_bounds__(kGmBlock) k_gm_first(int64_t n, const T *__restrict__ V0,
+                                                       const double *__restrict__ coef,
+                                                       const T *__restrict__ w, T *__restrict__ out,
+                                                       double *__restrict__ host) {
     using P = typename PairOf<T>::type;
-    __shared__ double red[kGmBlock / 64];
-    double cf[L], cc = 0.0;
-#pragma unroll
-    for (int i = 0; i < L; ++i) {
-        cf[i] = coef[i];
-        cc += cf[i] * cf[i];
+    const double pv = coef[0], ww = coef[1], est = ww - pv * pv;
+    const double c = est > 1e-4 * ww ? 1.0 / sqrt(est) : (ww > 0.0 ? 1.0 / sqrt(ww) : 0.0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        host[0] = pv;
+        host[1] = ww;
+        host[kGmScal + 2] = c;
     }
-    const double vv = coef[L], est = vv - cc;
-    const double inv = est > 1e-4 * vv ? 1.0 / sqrt(est) : (vv > 0.0 ? 1.0 / sqrt(vv) : 0.0);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *inv_out = inv;
-    double sum = 0.0;
     const int64_t np = n >> 1, stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < np; p += stride) {
-        const P vp = reinterpret_cast<const P *>(v)[p];
-        double x0 = (double)vp.x, x1 = (double)vp.y;
-#pragma unroll
-        for (int i = 0; i < L; ++i) {
-            const P xp = reinterpret_cast<const P *>(X + i * ld)[p];
-            x0 -= cf[i] * (double)xp.x;
-            x1 -= cf[i] * (double)xp.y;
-        }
+        const P wp = reinterpret_cast<const P *>(w)[p], xp = reinterpret_cast<const P *>(V0)[p];
         P o;
-        o.x = (T)(x0 * inv);
-        o.y = (T)(x1 * inv);
+        o.x = (T)(((double)wp.x - pv * (double)xp.x) * c);
+        o.y = (T)(((double)wp.y - pv * (double)xp.y) * c);
         reinterpret_cast<P *>(out)[p] = o;
-        sum += (double)o.x * (double)o.x + (double)o.y * (double)o.y;
     }
-    if ((n & 1) && blockIdx.x == 0 && threadIdx.x == 0) {
-        double x = (double)v[n - 1];
-#pragma unroll
-        for (int i = 0; i < L; ++i) x -= cf[i] * (double)X[i * ld + n - 1];
-        const T xt = (T)(x * inv);
-        out[n - 1] = xt;
-        sum += (double)xt * (double)xt;
+    if ((n & 1) && blockIdx.x == 0 && threadIdx.x == 0)
+        out[n - 1] = (T)(((double)w[n - 1] - pv * (double)V0[n - 1]) * c);
+}
+
+// r = b - w (b without w) and part[blk] = r . r in one pass (any alignment).
+template <typename T>
+__global__ void __launch_bounds__(kGmBlock) k_gm_resid(int64_t n, const T *__restrict__ b,
+                                                       const T *__restrict__ w, T *__restrict__ r,
+                                                       double *__restrict__ part) {
+    __shared__ double red[kGmBlock / 64];
+    double sum = 0.0;
+    for (int64_t q = (int64_t)blockIdx.x * kGmBlock + threadIdx.x; q < n;
+         q += (int64_t)gridDim.x * kGmBlock) {
+        const T rq = w ? (T)((double)b[q] - (double)w[q]) : b[q];
+        r[q] = rq;
+        sum += (double)rq * (double)rq;
     }
     sum = gm_block_sum(sum, red);
     if (threadIdx.x == 0) part[blockIdx.x] = sum;
 }
 
-// dst = src * scale[0] (scale from device memory, 1/sqrt of it when inv_sqrt)
+// dst = src * sc
 template <typename TS, typename TD>
-__global__ void k_gm_scale(int64_t n, const TS *__restrict__ src, TD *__restrict__ dst,
-                           const double *__restrict__ scale, int inv_sqrt) {
-    const double sc = inv_sqrt ? 1.0 / sqrt(scale[0]) : scale[0];
+__global__ void k_gm_scale(int64_t n, const TS *__restrict__ src, TD *__restrict__ dst, double sc) {
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n;
          q += (int64_t)gridDim.x * blockDim.x)
         dst[q] = (TD)((double)src[q] * sc);
-}
-
-// x += sum_i y_i Z_i (i < l)
-template <typename TZ, typename TX>
-__global__ void k_gm_update(int64_t n, int l, int64_t ld, const TZ *__restrict__ Z,
-                            const double *__restrict__ y, TX *__restrict__ x) {
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        double s = (double)x[q];
-        for (int i = 0; i < l; ++i) s += y[i] * (double)Z[i * ld + q];
-        x[q] = (TX)s;
-    }
 }
 
 // Cyclic Jacobi eigenvalue method for a symmetric n x n matrix A (row
@@ -1218,6 +1202,10 @@ struct sem_gmres_s {
     double *V = nullptr, *Z = nullptr, *w = nullptr, *r = nullptr;
     double *part = nullptr, *coef = nullptr;
     float *rhs32 = nullptr, *d32 = nullptr;
+    // pinned: the values of coef that the host reads, as in coef, and behind
+    // them the coefficients of a cycle's end on their way to the device
+    double *host = nullptr;
+    hipEvent_t event = nullptr;
     std::string err;
 };
 
@@ -1481,6 +1469,8 @@ extern "C" sem_status sem_gmres_create(sem_ctx c, int restart, sem_gmres *out) {
 extern "C" void sem_gmres_free(sem_gmres G) {
     if (!G) return;
     sem_free(G->coarse);
+    if (G->event) (void)hipEventDestroy(G->event);
+    if (G->host) (void)hipHostFree(G->host);
     delete G;
 }
 
@@ -1588,6 +1578,10 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
     sem_ctx c = G->ctx;
     hipStream_t s = (hipStream_t)stream;
     char *w = static_cast<char *>(dev);
+    if (!G->host)
+        SEM_HIP(c, hipHostMalloc((void **)&G->host, 8 * (kGmCoef + kGmMaxVec),
+                                 hipHostMallocMapped | hipHostMallocCoherent));
+    if (!G->event) SEM_HIP(c, hipEventCreateWithFlags(&G->event, hipEventDisableTiming));
     G->ws = w;
     G->ws_bytes = bytes;
     sem_status st = sem_bind_workspace(G->coarse, w + off[0], G->coarse_ws, stream);
@@ -1672,9 +1666,9 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
 
 // z from the local solutions (o null: without them) and the coarse solution.
 template <typename VT, typename I>
-static sem_status combine(sem_gmres G, const VT *o, bool coarse, VT *z, hipStream_t s) {
+static sem_status combine(sem_gmres G, const VT *o, bool coarse, VT *z, VT *clear, hipStream_t s) {
     sem_ctx c = G->ctx;
-    SumParams<VT, I> P{o, z, coarse ? G->x0 : nullptr, G->dcmap, G->dxi, G->dnbr,
+    SumParams<VT, I> P{o, z, clear, coarse ? G->x0 : nullptr, G->dcmap, G->dxi, G->dnbr,
                        static_cast<const I *>(G->doff), static_cast<const I *>(G->dpos),
                        dptr<int32_t>(c, c->L.bpos2l), G->dfirst, c->E, c->n_bnd};
     const dim3 g((unsigned)((c->E + kGmBlock / 64 - 1) / (kGmBlock / 64))), t(kGmBlock);
@@ -1692,11 +1686,13 @@ static sem_status combine(sem_gmres G, const VT *o, bool coarse, VT *z, hipStrea
     return SEM_OK;
 }
 
-// z = M^-1 r: parts & 1 local Schwarz solves, parts & 2 coarse grid.  r and
+// z = M^-1 r: parts & 1 local Schwarz solves, parts & 2 coarse grid; the
+// boundary block of `clear`, if given, is cleared on the way.  r and
 // z are FP64 or FP32 vectors; the local solves compute in the vectors'
 // precision, the coarse grid in FP64 either way.
 template <typename VT>
-static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, hipStream_t s) {
+static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, hipStream_t s,
+                               VT *clear = nullptr) {
     sem_ctx c = G->ctx;
     const int64_t n = c->n_unique;
     const bool local = parts & SEM_PC_SCHWARZ, coarse = parts & SEM_PC_COARSE;
@@ -1750,8 +1746,8 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
         // leave b0 cleared for the next application)
         SEM_HIP(c, coarse_solve(G->cplan, s));
     }
-    return wide_positions(G) ? combine<VT, uint64_t>(G, local ? o : nullptr, coarse, z, s)
-                             : combine<VT, uint32_t>(G, local ? o : nullptr, coarse, z, s);
+    return wide_positions(G) ? combine<VT, uint64_t>(G, local ? o : nullptr, coarse, z, clear, s)
+                             : combine<VT, uint32_t>(G, local ? o : nullptr, coarse, z, clear, s);
 }
 
 extern "C" sem_status sem_gmres_precondition(sem_gmres G, const double *r, double *z,
@@ -1801,16 +1797,16 @@ static unsigned resident_grid(K kern, int &per_cu, int ncu, int64_t n) {
     M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15) M(16)    \
     M(17) M(18) M(19) M(20) M(21) M(22) M(23) M(24) M(25) M(26) M(27) M(28) M(29) M(30) M(31)
 
-// coef[i] = X_i . v (i < L), coef[L] = v.v
+// coef[i] = X_i . v (i < L), coef[L] = v.v; also in host[0..L] if given
 template <int L, typename T>
 struct GmDots {
-    static hipError_t run(sem_gmres G, const T *X, const T *v, hipStream_t s) {
+    static hipError_t run(sem_gmres G, const T *X, const T *v, double *host, hipStream_t s) {
         static int per_cu = 0;
         const int64_t n = G->ctx->n_unique;
         const unsigned g = resident_grid(k_gm_dots<L, T>, per_cu, G->ctx->num_cus, n / 2);
         hipLaunchKernelGGL((k_gm_dots<L, T>), dim3(g), dim3(kGmBlock), 0, s, n, G->ld, X, v, G->part);
         hipLaunchKernelGGL(k_gm_finish, dim3(L + 1), dim3(kGmBlock), 0, s, (int)g,
-                           (const double *)G->part, G->coef);
+                           (const double *)G->part, G->coef, host);
         return hipGetLastError();
     }
 };
@@ -1838,13 +1834,13 @@ struct GmDots2 {
         hipLaunchKernelGGL((k_gm_dots2<L, T>), dim3(g), dim3(kGmBlock), 0, s, n, G->ld, X, vt, w,
                            G->part);
         hipLaunchKernelGGL(k_gm_finish, dim3(2 * L + 3), dim3(kGmBlock), 0, s, (int)g,
-                           (const double *)G->part, G->coef + kGmD);
+                           (const double *)G->part, G->coef + kGmD, (double *)nullptr);
         return hipGetLastError();
     }
 };
 
 // vt <- final basis vector, out <- next once-projected vector (from coef[kGmD..]);
-// beta, h, c to coef[kGmScal..]
+// all of them and beta, h, c to the host
 template <int L, typename T>
 struct GmUpdate2 {
     static hipError_t run(sem_gmres G, const T *X, T *vt, const T *w, T *out, hipStream_t s) {
@@ -1852,7 +1848,7 @@ struct GmUpdate2 {
         const int64_t n = G->ctx->n_unique;
         const unsigned g = resident_grid(k_gm_update2<L, T>, per_cu, G->ctx->num_cus, n / 2);
         hipLaunchKernelGGL((k_gm_update2<L, T>), dim3(g), dim3(kGmBlock), 0, s, n, G->ld, X,
-                           (const double *)(G->coef + kGmD), vt, w, out, G->coef + kGmScal);
+                           (const double *)(G->coef + kGmD), vt, w, out, G->host);
         return hipGetLastError();
     }
 };
@@ -1869,62 +1865,69 @@ static hipError_t gm_dispatch(int l, A... a) {
     }
 }
 
-// coef[0] = v.v (FP64 sum; v of any alignment)
+// What the host reads -- Gram-Schmidt sums, norms -- is written to pinned
+// memory by the kernel that forms it: gm_mark after that kernel, gm_wait before
+// reading (work queued in between runs on).
+static sem_status gm_mark(sem_gmres G, hipStream_t s) {
+    SEM_HIP(G->ctx, hipEventRecord(G->event, s));
+    return SEM_OK;
+}
+static sem_status gm_wait(sem_gmres G) {
+    SEM_HIP(G->ctx, hipEventSynchronize(G->event));
+    return SEM_OK;
+}
+
+// *out = v.v (FP64 sum; v of any alignment)
 template <typename T>
-static hipError_t gm_norm2(sem_gmres G, const T *v, hipStream_t s) {
+static sem_status gm_norm2(sem_gmres G, const T *v, double *out, hipStream_t s) {
     static int per_cu = 0;
     const int64_t n = G->ctx->n_unique;
     const unsigned g = resident_grid(k_gm_norm2<T>, per_cu, G->ctx->num_cus, n);
     hipLaunchKernelGGL(k_gm_norm2<T>, dim3(g), dim3(kGmBlock), 0, s, n, v, G->part);
     hipLaunchKernelGGL(k_gm_finish, dim3(1), dim3(kGmBlock), 0, s, (int)g, (const double *)G->part,
-                       G->coef);
-    return hipGetLastError();
+                       G->coef, G->host);
+    SEM_HIP(G->ctx, hipGetLastError());
+    sem_status e = gm_mark(G, s);
+    if (!e) e = gm_wait(G);
+    *out = G->host[0];
+    return e;
 }
 
 // First Arnoldi step of a cycle (V_0 final, no vector awaiting its second
-// projection): coef[0] = p = V_0 . w, coef[1] = w.w, then
-// out = (w - p V_0) * c with c = 1/sqrt(w.w - p^2) (or 1/|w|), c stored
-// at coef[kGmScal + 2].
+// projection): see k_gm_first.
 template <typename T>
 static hipError_t gm_first_step(sem_gmres G, const T *V0, const T *w, T *out, hipStream_t s) {
     static int per_cu = 0;
     const int64_t n = G->ctx->n_unique;
-    hipError_t e = GmDots<1, T>::run(G, V0, w, s);
+    hipError_t e = GmDots<1, T>::run(G, V0, w, nullptr, s);
     if (e != hipSuccess) return e;
-    const unsigned g = resident_grid(k_gm_orth_scale<1, T>, per_cu, G->ctx->num_cus, n / 2);
-    hipLaunchKernelGGL((k_gm_orth_scale<1, T>), dim3(g), dim3(kGmBlock), 0, s, n, G->ld, V0,
-                       (const double *)G->coef, w, out, G->part, G->coef + kGmScal + 2);
+    const unsigned g = resident_grid(k_gm_first<T>, per_cu, G->ctx->num_cus, n / 2);
+    hipLaunchKernelGGL(k_gm_first<T>, dim3(g), dim3(kGmBlock), 0, s, n, V0, (const double *)G->coef, w,
+                       out, G->host);
     return hipGetLastError();
-}
-
-// Host copy of coef[0] after the stream has reached it.
-static sem_status read_coef(sem_gmres G, int at, double *out, hipStream_t s) {
-    SEM_HIP(G->ctx, hipMemcpyAsync(out, G->coef + at, 8, hipMemcpyDeviceToHost, s));
-    SEM_HIP(G->ctx, hipStreamSynchronize(s));
-    return SEM_OK;
 }
 
 // r = b - A x in T vectors; returns ||r|| in *rn.
 template <typename T>
 static sem_status residual(sem_gmres G, int prec, const T *b, const T *x, T *r, T *w, bool x_zero,
                            double *rn, hipStream_t s) {
+    static int per_cu = 0;
     sem_ctx c = G->ctx;
     const int64_t n = c->n_unique;
-    SEM_HIP(c, hipMemcpyAsync(r, b, sizeof(T) * n, hipMemcpyDeviceToDevice, s));
     if (!x_zero) {
         sem_status e = apply_A<T>(G, prec, x, w, s);
         if (e) return e;
-        const double minus1 = -1.0;
-        SEM_HIP(c, hipMemcpyAsync(G->coef + kGmMisc, &minus1, 8, hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL((k_gm_update<T, T>), dim3(gm_grid(n)), dim3(kGmBlock), 0, s, n, 1, G->ld,
-                           (const T *)w, (const double *)(G->coef + kGmMisc), r);
-        SEM_HIP(c, hipGetLastError());
     }
-    SEM_HIP(c, gm_norm2<T>(G, r, s));
-    double rr = 0.0;
-    sem_status e = read_coef(G, 0, &rr, s);
+    const unsigned g = resident_grid(k_gm_resid<T>, per_cu, c->num_cus, n);
+    hipLaunchKernelGGL(k_gm_resid<T>, dim3(g), dim3(kGmBlock), 0, s, n, b,
+                       x_zero ? (const T *)nullptr : (const T *)w, r, G->part);
+    hipLaunchKernelGGL(k_gm_finish, dim3(1), dim3(kGmBlock), 0, s, (int)g, (const double *)G->part,
+                       G->coef, G->host);
+    SEM_HIP(c, hipGetLastError());
+    sem_status e = gm_mark(G, s);
+    if (!e) e = gm_wait(G);
     if (e) return e;
-    *rn = std::sqrt(rr);
+    *rn = std::sqrt(G->host[0]);
     return SEM_OK;
 }
 
@@ -1962,9 +1965,7 @@ static sem_status fgmres(sem_gmres G, int prec, const T *b, T *x, bool x_zero, d
         g(m + 1), y(m);
     for (;;) {
         const double inv = 1.0 / beta;                 // V_0 = r / beta
-        SEM_HIP(c, hipMemcpyAsync(G->coef + kGmMisc + 1, &inv, 8, hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL((k_gm_scale<T, T>), dim3(grid), dim3(kGmBlock), 0, s, n, (const T *)r, V,
-                           (const double *)(G->coef + kGmMisc + 1), 0);
+        hipLaunchKernelGGL((k_gm_scale<T, T>), dim3(grid), dim3(kGmBlock), 0, s, n, (const T *)r, V, inv);
         std::fill(H.begin(), H.end(), 0.0);
         std::fill(g.begin(), g.end(), 0.0);
         g[0] = beta;
@@ -2008,33 +2009,53 @@ static sem_status fgmres(sem_gmres G, int prec, const T *b, T *x, bool x_zero, d
             const double den = std::hypot(col[k], col[k + 1]);
             return den > 0 ? std::fabs(col[k + 1] / den * g[k]) : std::fabs(g[k]);
         };
+        // z_j = M^-1 v_j and w = A z_j
+        auto expand = [&](int j) -> sem_status {
+            T *Zj = Z + (size_t)j * ld;
+            sem_status st = precondition<T>(G, V + (size_t)j * ld, Zj, SEM_PC_SCHWARZ | SEM_PC_COARSE, s, w);
+            if (st) return st;
+            SEM_HIP(c, launch_ax(c, prec, Zj, w, 0, OUT_ATOMIC, nullptr, nullptr, c->tile[prec], s));
+            return SEM_OK;
+        };
+        // a non-finite step: whatever is queued has ended before the return
+        auto nan_step = [&]() {
+            (void)hipStreamSynchronize(s);
+            return gfail(G, SEM_ERR_NAN, "non-finite Arnoldi vector");
+        };
         int jdone = 0;
+        bool ahead = false;                              // step j's expansion is queued
+        double est0 = beta, est1 = beta;                 // estimates of the last two steps
         for (int j = 0; j < m; ++j) {
-            T *Vj = V + (size_t)j * ld, *Zj = Z + (size_t)j * ld, *Vn = V + (size_t)(j + 1) * ld;
-            e = precondition<T>(G, Vj, Zj, SEM_PC_SCHWARZ | SEM_PC_COARSE, s);
-            if (e) return e;
-            e = apply_A<T>(G, prec, Zj, w, s);
-            if (e) return e;
-            double d[kGmScal + 3 - kGmD];
+            T *Vj = V + (size_t)j * ld, *Vn = V + (size_t)(j + 1) * ld;
+            if (!ahead && (e = expand(j))) return e;
             if (j == 0) {
                 SEM_HIP(c, gm_first_step<T>(G, V, w, Vn, s));
-                double d0[2], cc = 0.0;
-                SEM_HIP(c, hipMemcpyAsync(d0, G->coef, 16, hipMemcpyDeviceToHost, s));
-                SEM_HIP(c, hipMemcpyAsync(&cc, G->coef + kGmScal + 2, 8, hipMemcpyDeviceToHost, s));
-                SEM_HIP(c, hipStreamSynchronize(s));
-                if (!std::isfinite(d0[0]) || !std::isfinite(d0[1]) || !std::isfinite(cc))
-                    return gfail(G, SEM_ERR_NAN, "non-finite Arnoldi vector");
+            } else {
+                SEM_HIP(c, (gm_dispatch<GmDots2, T>(j, G, (const T *)V, (const T *)Vj, (const T *)w, s)));
+                SEM_HIP(c, (gm_dispatch<GmUpdate2, T>(j, G, (const T *)V, Vj, (const T *)w, Vn, s)));
+            }
+            e = gm_mark(G, s);
+            if (e) return e;
+            // The next expansion needs none of the numbers that the host waits
+            // for, so it is queued before the wait, unless this step is
+            // expected to be the cycle's last (the reduction of the step
+            // before, once more, would reach atol): the read-back and some
+            // twenty launches, 30 to 56 us a step on small meshes, are hidden.
+            ahead = j + 1 < m && info->iterations + 1 < max_iter &&
+                    (j == 0 || est1 * std::min(1.0, est1 / est0) > atol);
+            if (ahead && (e = expand(j + 1))) return e;
+            e = gm_wait(G);
+            if (e) return e;
+            if (j == 0) {
+                const double *d0 = G->host, cc = G->host[kGmScal + 2];
+                if (!std::isfinite(d0[0]) || !std::isfinite(d0[1]) || !std::isfinite(cc)) return nan_step();
                 Hr[0] = d0[0];
                 hs[0] = cc > 0 ? 1.0 / cc : 0.0;
             } else {
                 const int L = j;
-                SEM_HIP(c, (gm_dispatch<GmDots2, T>(L, G, (const T *)V, (const T *)Vj, (const T *)w, s)));
-                SEM_HIP(c, (gm_dispatch<GmUpdate2, T>(L, G, (const T *)V, Vj, (const T *)w, Vn, s)));
-                SEM_HIP(c, hipMemcpyAsync(d, G->coef + kGmD, sizeof(d), hipMemcpyDeviceToHost, s));
-                SEM_HIP(c, hipStreamSynchronize(s));
-                const double *sc = d + (kGmScal - kGmD);
+                const double *d = G->host + kGmD, *sc = G->host + kGmScal;
                 for (int q = 0; q < 2 * L + 3; ++q)
-                    if (!std::isfinite(d[q])) return gfail(G, SEM_ERR_NAN, "non-finite Arnoldi vector");
+                    if (!std::isfinite(d[q])) return nan_step();
                 complete(j - 1, d, sc[0]);               // q = d[0..L), beta = sc[0]
                 if (sc[0] == 0.0) {                      // the vector lies in span(V): done
                     jdone = j;
@@ -2049,13 +2070,17 @@ static sem_status fgmres(sem_gmres G, int prec, const T *b, T *x, bool x_zero, d
             jdone = j + 1;
             const double est = estimate(j);
             info->rel_residual = est;
+            est0 = est1;
+            est1 = est;
             if (est <= atol || info->iterations >= max_iter || j + 1 == m || hs[j] == 0) {
                 // closing sweep: second projection of the vector in slot j+1
                 double q[kGmMaxVec + 1] = {}, beta_j = 0.0;
                 if (hs[j] > 0) {
-                    SEM_HIP(c, (gm_dispatch<GmDots, T>(j + 1, G, (const T *)V, (const T *)Vn, s)));
-                    SEM_HIP(c, hipMemcpyAsync(q, G->coef, 8 * (j + 2), hipMemcpyDeviceToHost, s));
-                    SEM_HIP(c, hipStreamSynchronize(s));
+                    SEM_HIP(c, (gm_dispatch<GmDots, T>(j + 1, G, (const T *)V, (const T *)Vn, G->host, s)));
+                    e = gm_mark(G, s);
+                    if (!e) e = gm_wait(G);
+                    if (e) return e;
+                    std::copy(G->host, G->host + j + 2, q);
                     double qq = 0.0;
                     for (int i = 0; i <= j; ++i) qq += q[i] * q[i];
                     const double b2 = q[j + 1] - qq;
@@ -2074,7 +2099,8 @@ static sem_status fgmres(sem_gmres G, int prec, const T *b, T *x, bool x_zero, d
             for (int k = i + 1; k < jdone; ++k) sum -= H[(size_t)i * m + k] * y[k];
             y[i] = sum / H[(size_t)i * m + i];
         }
-        SEM_HIP(c, hipMemcpyAsync(G->coef, y.data(), 8 * jdone, hipMemcpyHostToDevice, s));
+        std::copy(y.begin(), y.begin() + jdone, G->host + kGmCoef);
+        SEM_HIP(c, hipMemcpyAsync(G->coef, G->host + kGmCoef, 8 * jdone, hipMemcpyHostToDevice, s));
         SEM_HIP(c, (gm_dispatch<GmXupd, T>(jdone, G, (const T *)Z, x, s)));
         if (one_cycle) {
             *res_out = std::fabs(g[jdone]);
@@ -2116,10 +2142,9 @@ extern "C" sem_status sem_gmres_solve(sem_gmres G, const double *b, double *x,
         return info->status = st;
     };
     double bn = 0.0;
-    SEM_HIP(c, gm_norm2<double>(G, b, s));
     {
         double bb = 0.0;
-        sem_status e = read_coef(G, 0, &bb, s);
+        sem_status e = gm_norm2<double>(G, b, &bb, s);
         if (e) return done(e);
         bn = std::sqrt(bb);
     }
@@ -2173,9 +2198,8 @@ extern "C" sem_status sem_gmres_solve(sem_gmres G, const double *b, double *x,
         prev = rn;
         // inner right-hand side r / ||r|| in FP32
         const double inv = 1.0 / rn;
-        SEM_HIP(c, hipMemcpyAsync(G->coef + kGmMisc + 1, &inv, 8, hipMemcpyHostToDevice, s));
         hipLaunchKernelGGL((k_gm_scale<double, float>), dim3(gm_grid(n)), dim3(kGmBlock), 0, s, n,
-                           (const double *)G->r, G->rhs32, (const double *)(G->coef + kGmMisc + 1), 0);
+                           (const double *)G->r, G->rhs32, inv);
         SEM_HIP(c, hipGetLastError());
         double rin = 0.0;
         if (cur != prec) ++info->fp32_outer;

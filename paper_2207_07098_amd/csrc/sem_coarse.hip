@@ -9,14 +9,22 @@
 // cleared vector, a fixed summation order, and
 //  * up to 1024 rows: one workgroup does everything, one row per lane, the
 //    row's entries in registers and p in LDS (three barriers per iteration);
-//  * above: two kernels per iteration.  Each workgroup sums the partial sums
-//    of the preceding kernel itself and takes the scalar CG step; workgroup 0
-//    leaves the new state in the slot of this half iteration, which only the
-//    next kernel reads, so no launch is spent on a reduction.
+//  * up to 32768 rows of at most 28 entries: PCG with a single reduction, one
+//    kernel per iteration, four lanes to a row;
+//  * above: two kernels per iteration, one lane to a row.
+// Each workgroup sums the partial sums of the preceding kernel itself and takes
+// the scalar CG step; workgroup 0 leaves the new state in the slot of this
+// (half) iteration, which only the next kernel reads, so no launch is spent on
+// a reduction.
 // Nothing waits on the host.
 // GPU time of one application (8^3 elements, 729 rows; 21x18x16, 7106 rows;
-// 48^3, 117,649 rows): 29 / 99 / 155 us, before 260 / 250 / 500 us and a host
-// round trip.
+// 48^3, 117,649 rows): 29 / 68 / 155 us, as element-based CG 260 / 250 / 500 us
+// and a host round trip.  The kernels of the two larger forms, one kernel and
+// two per iteration: 3375 rows 68 and 97 us, 15625 rows 74 and 100, 24389 rows
+// 89 and 102, 35937 rows 113 and 104 (32 bytes per neighbour instead of 8; at
+// 117,649 rows 26.6 us an iteration instead of 15.4), hence the limit.  The
+// one-workgroup form does not gain from the single reduction (28.8 us either
+// way).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -32,6 +40,10 @@ namespace {
 constexpr int kCsBlock = 256;
 constexpr int kCsOneRows = 1024, kCsOneWidth = 27;   // limits of the one-workgroup solve
 constexpr int kCsStates = 2 * kCoarseIterations;
+// Single-reduction form over several workgroups: entries per lane (of the four
+// that share a row) and the rows up to which it is used.
+constexpr int kStepSlots = 7;
+constexpr int64_t kStepRows = 32768;
 
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -44,6 +56,13 @@ struct CsArgs {
     double *partA, *partB;        // [blocks][3], [blocks][2]
     CgState *st;                  // [kCsStates]
     int nblocks;
+    struct CsRow *q0, *q1;        // single-reduction form: rows before and after a step
+};
+
+// What a neighbour needs to form u = M^-1 r of a row after the step: one
+// gather of 32 bytes.
+struct __align__(32) CsRow {
+    double r, w, s, dinv;
 };
 
 // Sums of NV values over the workgroup (whole waves), one barrier; a barrier
@@ -171,6 +190,130 @@ __global__ void __launch_bounds__(kCsOneRows) k_cs_one(CsArgs P) {
         P.st[kCsStates - 1].status = S.status;
         P.st[kCsStates - 1].done = S.done;
     }
+}
+
+// Scalars of the single-reduction form (Chronopoulos and Gear) from gamma =
+// r.u, delta = u.A u and r.r of the current residual, u = M^-1 r: beta as
+// usual, p.A p = delta - beta^2 (p.A p)' with (p.A p)' of the step before.
+__device__ __forceinline__ void cs_scalars(CgState &S, bool first, double gamma, double delta,
+                                           double rr) {
+    if (first) {
+        cs_init(S);
+        cg_finish_begin(S, gamma, rr, rr);
+        if (!S.done) cg_finish_ax(S, delta);
+        return;
+    }
+    const double before = S.pAp;
+    cg_finish_update(S, rr, gamma);
+    if (!S.done) cg_finish_ax(S, delta - S.beta * S.beta * before);
+}
+
+// The single-reduction form over several workgroups, one kernel per iteration
+// and one before.  kStepInit: w = A u for r = b; the others sum the partials
+// of the kernel before, step, and form w = A u of the new residual, of which
+// every row computes its neighbours' u itself, u_j = dinv_j (r_j - alpha (w_j +
+// beta s_j)), from the old rows (two buffers in turn).  kStepLast only needs x.
+// Four lanes share a row, kStepSlots entries each, so that all loads of a row
+// are requested at once, before the sums: the kernel is a chain of three loads
+// and a sum, 256 lanes to 64 rows.
+enum { kStepInit, kStepFirst, kStepNext, kStepLast };
+template <int MODE>
+__global__ void __launch_bounds__(kCsBlock) k_cs_step(CsArgs P, int it) {
+    __shared__ double red[3][16];
+    __shared__ CgState sh;
+    const int sub = threadIdx.x & 3;
+    const int64_t i = (int64_t)blockIdx.x * (kCsBlock / 4) + (threadIdx.x >> 2);
+    const bool on = i < P.n;
+    const CsRow *old = (it & 1) ? P.q1 : P.q0;
+    CsRow *next = MODE == kStepInit ? P.q0 : ((it & 1) ? P.q0 : P.q1);
+    int stopped = 0;
+    double t[3] = {0.0, 0.0, 0.0};
+    if constexpr (MODE == kStepNext || MODE == kStepLast) stopped = P.st[it - 1].done;
+    if (MODE != kStepInit && !stopped)
+        cs_load_partials<3>((it & 1) ? P.partB : P.partA, P.nblocks, t);
+    double a[kStepSlots];
+    CsRow nb[kStepSlots], me{0.0, 0.0, 0.0, 0.0};
+    double p = 0.0, x = 0.0;
+    const bool matrix = MODE != kStepLast;
+    if (on && !stopped) {
+        if constexpr (MODE == kStepInit) {
+            me.r = P.b[i];
+            me.dinv = P.dinv[i];
+        } else {
+            me = old[i];
+            if constexpr (MODE != kStepFirst) {
+                p = P.p[i];
+                x = P.x[i];
+            }
+        }
+        if (matrix) {
+            int j[kStepSlots];
+#pragma unroll
+            for (int s = 0; s < kStepSlots; ++s) {
+                const int c = sub + 4 * s;
+                j[s] = c < P.width ? P.idx[(size_t)c * P.ld + i] : (int)i;
+                a[s] = c < P.width ? P.val[(size_t)c * P.ld + i] : 0.0;
+            }
+#pragma unroll
+            for (int s = 0; s < kStepSlots; ++s) {
+                if constexpr (MODE == kStepInit) nb[s] = CsRow{P.b[j[s]], 0.0, 0.0, P.dinv[j[s]]};
+                else nb[s] = old[j[s]];
+            }
+        }
+    }
+    double alpha = 0.0, beta = 0.0;
+    if constexpr (MODE != kStepInit) {
+        if (!stopped) cs_block_sum<3>(t, red);
+        if (threadIdx.x == 0) {
+            if (MODE != kStepFirst) sh = P.st[it - 1];
+            if (!stopped) cs_scalars(sh, MODE == kStepFirst, t[0], t[1], t[2]);
+            if (blockIdx.x == 0) {
+                P.st[it] = sh;
+                if (MODE == kStepLast) P.st[kCsStates - 1] = sh;
+            }
+        }
+        __syncthreads();
+        if (MODE == kStepFirst && on && sub == 0) P.b[i] = 0.0;
+        if (sh.done) {
+            if (on && sub == 0 && !stopped) {
+                if (sh.status == CG_NONFINITE) P.x[i] = __builtin_nan("");
+                else if (MODE == kStepFirst) P.x[i] = 0.0;
+            }
+            return;
+        }
+        alpha = sh.alpha;
+        beta = sh.beta;
+    }
+    // this row's step
+    const double u0 = me.dinv * me.r;
+    if constexpr (MODE != kStepInit) {
+        p = u0 + beta * p;
+        if (on && sub == 0) {
+            P.x[i] = x + alpha * p;
+            if (matrix) P.p[i] = p;
+        }
+        if (!matrix) return;
+        me.s = me.w + beta * me.s;
+        me.r -= alpha * me.s;
+    }
+    const double u = me.dinv * me.r;
+    double w = 0.0;
+    if (on)
+#pragma unroll
+        for (int s = 0; s < kStepSlots; ++s)
+            w += a[s] * (nb[s].dinv * (nb[s].r - alpha * (nb[s].w + beta * nb[s].s)));
+    w += dpp_mov<0xb1>(w);                   // quad_perm [1,0,3,2]
+    w += dpp_mov<0x4e>(w);                   // quad_perm [2,3,0,1]
+    me.w = w;
+    if (on && sub == 0) next[i] = me;
+    const bool lead = on && sub == 0;
+    double g[3] = {lead ? me.r * u : 0.0, lead ? w * u : 0.0, lead ? me.r * me.r : 0.0};
+    __syncthreads();                         // red: the first sum has been read
+    cs_block_sum<3>(g, red);
+    double *part = MODE == kStepInit || (it & 1) ? P.partA : P.partB;
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) part[(size_t)blockIdx.x * 3 + c] = g[c];
 }
 
 // First half of iteration `it`: the scalar step after the residual update,
@@ -310,6 +453,8 @@ __global__ void __launch_bounds__(kCsBlock) k_cs_update(CsArgs P, int it) {
 }
 
 int cs_blocks(int64_t n) { return (int)((n + kCsBlock - 1) / kCsBlock); }
+int cs_step_blocks(int64_t n) { return (int)((n + kCsBlock / 4 - 1) / (kCsBlock / 4)); }
+bool cs_step_form(const CoarsePlan &p) { return p.n <= kStepRows && p.width <= 4 * kStepSlots; }
 
 }  // namespace
 
@@ -357,8 +502,12 @@ static size_t layout(const CoarsePlan &p, size_t (&off)[7]) {
     };
     off[0] = take(4 * (size_t)p.width * p.ld);
     off[1] = take(8 * (size_t)p.width * p.ld);
-    for (int q = 0; q < 4; ++q) off[2 + q] = take(8 * (size_t)p.n);     // r, z, w, p
-    off[6] = take(8 * 5 * (size_t)cs_blocks(p.n) + sizeof(CgState) * kCsStates + 256);
+    const bool step = cs_step_form(p);
+    // p, and r, z, w or the two buffers of rows
+    off[5] = take(8 * (size_t)p.n);
+    for (int q = 0; q < 3; ++q) off[2 + q] = take((step ? (q < 2 ? sizeof(CsRow) : 0) : 8) * (size_t)p.n);
+    off[6] = take(8 * (step ? 6 * (size_t)cs_step_blocks(p.n) : 5 * (size_t)cs_blocks(p.n)) +
+                  sizeof(CgState) * kCsStates + 256);
     return o;
 }
 
@@ -394,13 +543,24 @@ hipError_t coarse_bind(sem_ctx c, CoarsePlan &p, char *ws, double *b, double *x,
 }
 
 hipError_t coarse_solve(const CoarsePlan &p, hipStream_t s) {
+    const bool step = cs_step_form(p);
+    const int nb = step ? cs_step_blocks(p.n) : cs_blocks(p.n);
     CsArgs A{p.n, p.ld, p.width, p.idx, p.val, p.dinv, p.b, p.x, p.r, p.z, p.w, p.p,
-             p.part, p.part + 3 * (size_t)cs_blocks(p.n), p.state, cs_blocks(p.n)};
+             p.part, p.part + 3 * (size_t)nb, p.state, nb,
+             reinterpret_cast<CsRow *>(p.r), reinterpret_cast<CsRow *>(p.z)};
     if (p.n <= kCsOneRows && p.width <= kCsOneWidth) {
         hipLaunchKernelGGL(k_cs_one, dim3(1), dim3((unsigned)((p.n + 63) / 64 * 64)), 0, s, A);
         return hipGetLastError();
     }
-    const dim3 g((unsigned)cs_blocks(p.n)), t(kCsBlock);
+    const dim3 g((unsigned)nb), t(kCsBlock);
+    if (step) {
+        hipLaunchKernelGGL(k_cs_step<kStepInit>, g, t, 0, s, A, 0);
+        hipLaunchKernelGGL(k_cs_step<kStepFirst>, g, t, 0, s, A, 0);
+        for (int it = 1; it + 1 < kCoarseIterations; ++it)
+            hipLaunchKernelGGL(k_cs_step<kStepNext>, g, t, 0, s, A, it);
+        hipLaunchKernelGGL(k_cs_step<kStepLast>, g, t, 0, s, A, kCoarseIterations - 1);
+        return hipGetLastError();
+    }
     for (int it = 0; it < kCoarseIterations; ++it) {
         if (it == 0) {
             hipLaunchKernelGGL(k_cs_dir<true>, g, t, 0, s, A, it);

@@ -52,3 +52,47 @@ def test_non_finite_residual_is_reported(name):
     # and leaves nothing behind for the next application
     z = ps.precondition(torch.zeros_like(r), parts=ps.COARSE)
     assert float(z.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("K", [(32, 31, 30), (32, 31, 31)])
+def test_coarse_part_around_the_one_kernel_form(K):
+    """32,736 and 33,792 vertices, on both sides of the 32768 up to which an
+    iteration is one kernel: ten PCG iterations on the same operator, written
+    with tensor operations on an N = 1 context, to 1e-11 (the forms of the
+    recurrence differ by rounding only)."""
+    m = F.box(K, hi=(3.0, 2.0, 2.0))
+    op = sem.Operator(m, 2, precisions=("fp64",))
+    ps = sem.PressureSolver(op, restart=4)
+    r = op.ax(torch.rand(op.n_unique, generator=torch.Generator(device="cuda").manual_seed(1),
+                         dtype=torch.float64, device="cuda"))
+    z = ps.precondition(r, parts=ps.COARSE)
+    c = sem.Operator(m, 1, precisions=("fp64",))
+    gid, pos, _, _ = op.numbering()
+    cgid, cpos, cdm, _ = c.numbering()
+    x1 = np.array([-1.0, 0.0, 1.0])
+    h = np.stack([(1 - x1) / 2, (1 + x1) / 2])                     # [2][3]
+    P = np.einsum("ai,bj,ck->cbakji", h, h, h).reshape(8, 27)      # corner, point
+    rc = r.cpu().numpy()[pos]
+    first = np.zeros(gid.size, dtype=bool)
+    first[np.unique(gid.ravel(), return_index=True)[1]] = True     # one copy of each node
+    b = np.zeros(c.n_unique)
+    np.add.at(b, cgid.ravel(), ((rc[gid] * first.reshape(gid.shape)) @ P.T).ravel())
+    b[cdm == 1] = 0.0
+    bs = np.empty_like(b)
+    bs[cpos] = b
+    rv = torch.from_numpy(bs).cuda()
+    d = torch.from_numpy(c.geometry()[2]).cuda()
+    x, p = torch.zeros_like(rv), d * rv
+    rz = torch.dot(rv, p)
+    for _ in range(10):
+        w = c.ax(p)
+        a = rz / torch.dot(p, w)
+        x += a * p
+        rv = rv - a * w
+        rz, o = torch.dot(rv, d * rv), rz
+        p = d * rv + (rz / o) * p
+    xc = x.cpu().numpy()[cpos]
+    want = np.zeros(op.n_unique)
+    want[gid.ravel()] = (xc[cgid] @ P).ravel()
+    got = z.cpu().numpy()[pos]
+    assert relerr(got, want) < 1e-11

@@ -19,8 +19,9 @@
 //   * element-interior nodes have solver indices that follow from the
 //     element index, so only element-boundary points read an index map and
 //     only they are summed (device atomics or a fixed-order second pass);
-//   * element groups are dealt to the 8 XCDs in contiguous ranges so that
-//     neighbouring elements share each XCD's L2.
+//   * element groups go to the 8 XCDs round-robin, as the hardware deals
+//     workgroups: the factors are then read consecutively across the whole
+//     chip (contiguous ranges per XCD, a tile option, are up to 11% slower).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -154,36 +155,41 @@ __device__ void block_partial(const double (&v)[NV], double *partials) {
 }
 
 // Sum of the packed partials of nblocks blocks (NV values each) by one
-// workgroup: UF independent chains per thread keep that many loads in
-// flight; the order is fixed for a given nblocks.
+// workgroup, in a fixed order.  Bounded by the latency of its rounds of loads
+// (the partials lie in the L2s of eight XCDs): 16 bytes and UF chains per lane,
+// the last round's missing entries clamped and not added.
 template <int NV>
 __device__ __forceinline__ void sum_partials(const double *__restrict__ partials, int nblocks,
                                              double (&acc)[3]) {
+    typedef double pair_t __attribute__((ext_vector_type(2)));
     constexpr int UF = 8;
-    double accu[UF][NV] = {};
-    int q = threadIdx.x;
-    for (; q + (UF - 1) * (int)blockDim.x < nblocks; q += UF * blockDim.x) {
-        double v[UF][NV];
+    const int n = nblocks * NV, np = n >> 1;      // doubles, whole pairs
+    const pair_t *pp = reinterpret_cast<const pair_t *>(partials);
+    acc[0] = acc[1] = acc[2] = 0.0;
+    if constexpr (NV == 3) {
+        for (int q = threadIdx.x; q < nblocks; q += blockDim.x)
 #pragma unroll
-        for (int c = 0; c < UF; ++c)
+            for (int a = 0; a < 3; ++a) acc[a] += partials[(size_t)q * 3 + a];
+    } else {
+        pair_t accu[UF] = {};
+        for (int q = threadIdx.x; q < np; q += UF * blockDim.x) {
+            pair_t v[UF];
 #pragma unroll
-            for (int a = 0; a < NV; ++a) v[c][a] = partials[(size_t)(q + c * blockDim.x) * NV + a];
+            for (int c = 0; c < UF; ++c) v[c] = pp[min(q + c * (int)blockDim.x, np - 1)];
 #pragma unroll
-        for (int c = 0; c < UF; ++c)
-#pragma unroll
-            for (int a = 0; a < NV; ++a) accu[c][a] += v[c][a];
-    }
-    for (; q < nblocks; q += blockDim.x)
-#pragma unroll
-        for (int a = 0; a < NV; ++a) accu[0][a] += partials[(size_t)q * NV + a];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        double t = 0.0;
-        if (a < NV) {
-#pragma unroll
-            for (int c = 0; c < UF; ++c) t += accu[c][a < NV ? a : 0];
+            for (int c = 0; c < UF; ++c)
+                if (q + c * (int)blockDim.x < np) accu[c] += v[c];
         }
-        acc[a] = t;
+        pair_t t = accu[0];
+#pragma unroll
+        for (int c = 1; c < UF; ++c) t += accu[c];
+        if (NV == 2) {
+            acc[0] = t.x;
+            acc[1] = t.y;
+        } else {
+            acc[0] = t.x + t.y;
+            if ((n & 1) && threadIdx.x == 0) acc[0] += partials[n - 1];
+        }
     }
 }
 
@@ -207,9 +213,10 @@ __global__ void __launch_bounds__(1024) k_finish(int site, const double *__restr
     if (site == FIN_AX) sum_partials<1>(partials, nblocks, acc);
     else if (site == FIN_BEGIN) sum_partials<3>(partials, nblocks, acc);
     else sum_partials<2>(partials, nblocks, acc);
+    const int nv = site == FIN_AX ? 1 : (site == FIN_BEGIN ? 3 : 2);
     double out[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) out[a] = block_sum(acc[a], red);
+    for (int a = 0; a < 3; ++a) out[a] = a < nv ? block_sum(acc[a], red) : 0.0;
     if (threadIdx.x != 0) return;
     switch (site) {
         case FIN_AX: cg_finish_ax(*st, out[0]); break;                    // p^T A p -> alpha

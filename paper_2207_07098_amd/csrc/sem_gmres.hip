@@ -1694,7 +1694,6 @@ template <typename VT>
 static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, hipStream_t s,
                                VT *clear = nullptr) {
     sem_ctx c = G->ctx;
-    const int64_t n = c->n_unique;
     const bool local = parts & SEM_PC_SCHWARZ, coarse = parts & SEM_PC_COARSE;
     // with both parts the coarse restriction is summed in the local-solve
     // kernel's gather (the residual is read once)

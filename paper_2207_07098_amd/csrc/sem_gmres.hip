@@ -209,7 +209,7 @@ k_fdm_map(const int32_t *__restrict__ ghost, const int32_t *__restrict__ bmap,
 // operand of its backward pass (result row = the next contraction index; FP32
 // results lie at row 4 (lane / 16) + register, FP64 ones at 4 register + lane
 // / 16, and the operand A follows).  One wave per workgroup: its LDS
-// operations stay in order, so there are no barriers.
+// operations stay in order, so there are no workgroup barriers.
 //
 // What bounds it at NE = 10 in FP64: 126 MFMAs of 64 cycles per element (54% of
 // the kernel's SIMD cycles; 10 of 16 rows are used) and about 1150 vector
@@ -330,7 +330,7 @@ k_fdm(FdmParams<VT> P) {
             phi[1][lane] = in ? 0.5 * (1.0 + x) : 0.0;
         }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     VT v[T][KS];
 #pragma unroll
     for (int t = 0; t < T; ++t)
@@ -343,7 +343,7 @@ k_fdm(FdmParams<VT> P) {
     for (int x = 0; x < QS; ++x)
         if (lane + 64 * x < 3 * C) Sl[lane + 64 * x] = sr[x];
     if (lane < 3 * NE) lams[lane / NE][lane % NE] = lr0;
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     // ---- P^T r over the element's owned points: the t-shape functions on the
     // lane's points, then the r and s ones, one wave sum per corner
     if (P.b0) {
@@ -415,7 +415,7 @@ k_fdm(FdmParams<VT> P) {
                 buf[col < C && row < NE ? base + step * row : Sh::ROWS + lane] = acc[t][r];
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
     };
     auto get = [&](bool by_hi) {
         const int pitch = by_hi ? Sh::PHI : Sh::PLO;
@@ -425,7 +425,7 @@ k_fdm(FdmParams<VT> P) {
 #pragma unroll
             for (int t = 0; t < T; ++t) v[t][s] = buf[kc * pitch + 16 * t + j];
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
     };
     contract(2, true);                              // t forward: lines (a, b)
     put(true);
@@ -634,7 +634,7 @@ __global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT, I> P) {
 #pragma unroll
         for (int u = 0; u < QI; ++u)
             if (lane + 64 * u < NI) zb[lane + 64 * u] = (double)own[u];
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
 #pragma unroll
         for (int f = 0; f < 6; ++f) {
             if (nbe[f] < 0) continue;
@@ -645,7 +645,7 @@ __global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT, I> P) {
                 const int t = lane + 64 * u;
                 if (t < NF) zb[(f % 2 ? (NM - 1) * s[d] : 0) + t % NM * sp + t / NM * sq] += (double)ext[f][u];
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
         }
     }
     double xc[8];

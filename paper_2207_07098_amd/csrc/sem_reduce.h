@@ -1,11 +1,22 @@
-// Wave reductions on the vector ALUs (gfx950).  __shfl_xor goes through the
-// LDS pipe (two permutes of 32 bits per step of a double); DPP moves do not,
-// and their latency hides behind the next value's.
+// Wave reductions on the vector ALUs (gfx950) and the ordering of LDS accesses
+// between the lanes of one wave.  __shfl_xor goes through the LDS pipe (two
+// permutes of 32 bits per step of a double); DPP moves do not, and their
+// latency hides behind the next value's.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 namespace sem {
+
+// What a lane wrote to LDS before it, every lane of its wave reads after it.
+// The hardware runs a wave's LDS operations in order; the fences keep the
+// compiler from exchanging a store with another lane's load (the barrier alone
+// is no memory operation to it).  They cost no instruction at this scope.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // v of the lane that the DPP control selects, 0.0 where it selects none.
 template <int CTRL>

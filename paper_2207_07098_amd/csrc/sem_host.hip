@@ -111,10 +111,12 @@ extern "C" const char *sem_last_error(sem_ctx ctx) {
 }
 
 // Launch shape of the element operator before any sem_autotune, from timings
-// of every shape at N = 2..13 and 0.3, 2 and 16 million nodes (times below at
-// 16 million, FP64 unless another type is named; us):
-//  * one workgroup per element group and no XCD remap throughout (48^3, N = 7:
-//    623 against 690 remapped);
+// of every shape at N = 1..15, eight mesh sizes from 60 thousand to 14 million
+// nodes and more between them below 100 thousand (times in us, call included;
+// FP64 unless another type is named).  The assembled operator on unique
+// vectors:
+//  * one workgroup per element group and no XCD remap (48^3, N = 7: 623 against
+//    690 remapped);
 //  * FP64: small elements share a workgroup -- N = 2 eight per workgroup (1066
 //    against 1659 for one), N = 3 and 4 two (725 / 383 against 828 / 502),
 //    N = 5 three (343 against 394; seven: 349), N = 6 one (296; two: 299),
@@ -127,20 +129,39 @@ extern "C" const char *sem_last_error(sem_ctx ctx) {
 //    elements, where the launch is latency (512: 12.2 against 12.5);
 //  * FP64 from N = 8 and FP32 from N = 11: a ring of two factor planes (N = 9:
 //    267 against 439; N = 11 in FP32: 148 against 173).
-static AxTile default_tile(int N, int64_t E, int prec) {
+// The other forms differ where the shape decides what they wait for:
+//  * whole element blocks (ax_local and the first pass of the fixed-order sum):
+//    plain stores, nothing waits for atomics, and a workgroup of few lanes only
+//    leaves lanes idle.  E = 185,193, N = 3: ax_local in FP32 54.6 with four
+//    elements and 106 with one, FP16 36.8 and 84.7; N = 4 FP16 74 with five,
+//    122 with one; N = 5 FP64 372 with three, 395 with one (110,592 elements);
+//    N = 2 FP16 fixed order 161 with seven, 177 with four;
+//  * FP64 vectors around reduced factors: the gather outweighs the factors, and
+//    neighbours that share an L2 are worth the remap (34^3, N = 7: 148 against
+//    163; N = 8: 1.02 times slower with it);
+//  * Helmholtz at N = 9: with all planes in flight two workgroups fit a CU, and
+//    while that holds the whole mesh the ring only lengthens the chain (512
+//    elements 14.5 against 15.8; 729: 25.0 against 19.8).
+namespace sem {
+AxTile default_tile(int N, int64_t E, int prec, AxForm form, int num_cus) {
     AxTile t;
+    t.stock = true;
     t.xcd = 0;
-    const bool f64 = prec == SEM_FP64;
-    if (N == 1) t.epb = 16;
+    const bool f64 = prec == SEM_FP64, f16 = !f64 && prec != SEM_FP32;
+    if (N == 8) t.epb = E >= 2048 ? 3 : 1;
+    else if (form == AX_BLOCKS) t.epb = N >= 6 ? 1 : N == 5 ? 3 : N == 4 ? (f16 ? 5 : 2) : N == 3 ? 4 : N == 2 ? 7 : 16;
+    else if (N == 1) t.epb = 16;
     else if (N == 2) t.epb = f64 ? 8 : 4;
     else if (N <= 4) t.epb = f64 ? 2 : 1;
     else if (N == 5) t.epb = f64 ? 3 : 1;
     else if (N == 7) t.epb = f64 && E >= 32768 ? 2 : 1;
-    else if (N == 8) t.epb = E >= 2048 ? 3 : 1;
     else t.epb = 1;
     t.pipeline = (f64 && N >= 8) || (prec == SEM_FP32 && N >= 11) ? 1 : 0;
+    if (form == AX_HELM && N == 9 && E <= 2 * num_cus) t.pipeline = 0;
+    if (form == AX_MIXED && (N == 6 || N == 7)) t.xcd = 1;
     return t;
 }
+}  // namespace sem
 
 extern "C" sem_status sem_setup(const sem_mesh *mesh, int N, const sem_options *opts,
                                 sem_ctx *out) {
@@ -188,7 +209,7 @@ extern "C" sem_status sem_setup(const sem_mesh *mesh, int N, const sem_options *
     if (mesh->face_bc) c->face_bc.assign(mesh->face_bc, mesh->face_bc + 6 * c->E);
     else c->face_bc.assign(6 * c->E, 0);
     c->num_vertices = mesh->num_vertices;
-    for (int p = 0; p < kNumPrec; ++p) c->tile[p] = default_tile(N, c->E, p);
+    for (int p = 0; p < kNumPrec; ++p) c->tile[p] = default_tile(N, c->E, p, AX_UNIQUE, c->num_cus);
     *out = c;
     return SEM_OK;
 }
@@ -613,10 +634,14 @@ static bool tile_valid(sem_ctx c, int prec, const sem_tile &t) {
 extern "C" sem_status sem_set_tile(sem_ctx c, sem_precision prec, const sem_tile *t) {
     if (!c || !t || (int)prec < 0 || (int)prec >= kNumPrec) return fail(c, SEM_ERR_INVALID, "bad argument");
     if (!tile_valid(c, prec, *t)) return fail(c, SEM_ERR_INVALID, "tile does not fit this order");
-    c->tile[prec].epb = t->elements_per_block;
-    c->tile[prec].grid_cap = t->grid_cap;
-    c->tile[prec].xcd = t->xcd_remap;
-    c->tile[prec].pipeline = t->pipeline;
+    AxTile &o = c->tile[prec];
+    // what sem_get_tile returned, set again, changes nothing
+    o.stock = o.stock && o.epb == t->elements_per_block && o.grid_cap == t->grid_cap &&
+              o.xcd == t->xcd_remap && o.pipeline == t->pipeline;
+    o.epb = t->elements_per_block;
+    o.grid_cap = t->grid_cap;
+    o.xcd = t->xcd_remap;
+    o.pipeline = t->pipeline;
     for (auto &g : c->graphs) (void)hipGraphExecDestroy(g.exec);
     c->graphs.clear();
     return SEM_OK;

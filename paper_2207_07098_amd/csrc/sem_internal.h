@@ -44,7 +44,15 @@ struct AxTile {
     int grid_cap = 0;     // max workgroups (0: one per element group)
     int xcd = 1;          // XCD-aware element chunking
     int pipeline = 0;     // 0: all factor planes in flight; 1: a ring of 2 planes
+    bool stock = false;   // default_tile's: every form of the operator takes its own
 };
+
+// Forms of the operator whose launch shapes differ: the assembled operator on
+// unique vectors; the same with FP64 vectors around reduced-precision factors;
+// the Helmholtz operator; and the forms that store whole element blocks
+// (E-vectors and the fixed-order summation).
+enum AxForm { AX_UNIQUE = 0, AX_MIXED, AX_HELM, AX_BLOCKS };
+AxTile default_tile(int N, int64_t E, int prec, AxForm form, int num_cus);
 
 // Offset, in values, of factor component q (0..5 = 11,22,33,12,13,23) of
 // point (k, col = i + n1*j) of element e in a factor array of sz-byte

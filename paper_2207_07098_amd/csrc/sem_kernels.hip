@@ -1144,9 +1144,10 @@ hipError_t ax_dispatch_n(sem_ctx c, const void *Gp, const float *gscale, const v
     const bool early = sizeof(GS) < 8 && grid == P.ngroups;
     const dim3 g((unsigned)grid), b(threads);
     // the E-vector and fixed-order forms take the planes in flight that suit
-    // the order: all of them, in FP64 from N = 9 a ring of two (all planes run
-    // at one wave per SIMD there: 439 against 267 us at 28^3, N = 9)
-    constexpr int kFixedPF = sizeof(T) == 8 && N1 >= 10 ? 2 : N1;
+    // the order: a ring of two from N = 9 (FP64, N = 9, 28^3: all planes run at
+    // one wave per SIMD, 439 against 267 us; FP32 in fixed order, N = 11, 22^3:
+    // 176 and 154 us, N = 15, 16^3: 179 and 139), all of them below
+    constexpr int kFixedPF = N1 >= 10 ? 2 : N1;
 #define SEM_AXL(MODE, VT, PF, HELM)                                                            \
     do {                                                                                       \
         if (early)                                                                             \
@@ -2283,8 +2284,13 @@ hipError_t launch_rhs(sem_ctx c, const double *fL, const double *f, double *b, h
 }
 
 hipError_t launch_ax(sem_ctx c, int prec, const void *u, void *y, int in_local, int out_mode,
-                     double *partials, CgState *st, const AxTile &t, hipStream_t s, bool vec64,
+                     double *partials, CgState *st, const AxTile &tile, hipStream_t s, bool vec64,
                      int *fuse) {
+    const AxForm form = in_local || out_mode != OUT_ATOMIC ? AX_BLOCKS
+                        : c->helm                          ? AX_HELM
+                        : vec64 && prec != SEM_FP64        ? AX_MIXED
+                                                           : AX_UNIQUE;
+    const AxTile t = tile.stock ? default_tile(c->N, c->E, prec, form, c->num_cus) : tile;
     switch (prec) {
         case SEM_FP64:
             return ax_dispatch<double>(c, prec, u, y, in_local, out_mode, partials, st, t, s, vec64, fuse);

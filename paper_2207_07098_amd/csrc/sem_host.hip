@@ -115,11 +115,20 @@ extern "C" const char *sem_last_error(sem_ctx ctx) {
 // nodes and more between them below 100 thousand (times in us, call included;
 // FP64 unless another type is named).  The assembled operator on unique
 // vectors:
-//  * one workgroup per element group and no XCD remap (48^3, N = 7: 623 against
-//    690 remapped);
+//  * one workgroup per element group; without an XCD remap where the factors
+//    stream from HBM (48^3, N = 7: 623 against 690 remapped).  With it up to
+//    4096 elements, about one resident set of waves, where the gather's latency
+//    counts and neighbours share an L2 (N = 7, 2744 elements: 24.4 against
+//    25.1; N = 10 in FP32, 1000: 16.3 against 16.8), and in FP64 at the lowest
+//    orders, whose nodes are mostly shared (N = 3, 80^3: 563 against 646; N =
+//    2, 91^3: 6% less; N = 1 from half a million elements, 136^3: 297 against
+//    309, below that 2% more);
 //  * FP64: small elements share a workgroup -- N = 2 eight per workgroup (1066
 //    against 1659 for one), N = 3 and 4 two (725 / 383 against 828 / 502),
-//    N = 5 three (343 against 394; seven: 349), N = 6 one (296; two: 299),
+//    N = 5 three (343 against 394; seven: 349), but seven where they need one
+//    round of workgroups and three begin a second that is nearly empty (four
+//    workgroups of three and two of seven fit a CU; 3375 elements: 16.3
+//    against 18.2), N = 6 one (296; two: 299),
 //    N = 7 one up to 32768 elements (24^3: 83 against 88 for two) and two from
 //    there (48^3: 621 against 662);
 //  * 32- and 16-bit factors: N = 2 four (695 against 1090), N = 3 to 7 one (N
@@ -127,8 +136,11 @@ extern "C" const char *sem_last_error(sem_ctx ctx) {
 //  * N = 8: 81 lanes leave 47 of a second wave idle, three elements 13 of
 //    four waves (FP64 249 against 278, FP32 146 against 157), except on few
 //    elements, where the launch is latency (512: 12.2 against 12.5);
-//  * FP64 from N = 8 and FP32 from N = 11: a ring of two factor planes (N = 9:
-//    267 against 439; N = 11 in FP32: 148 against 173).
+//  * a ring of two factor planes: FP64 from N = 8 and FP32 from N = 11 (N = 9:
+//    267 against 439; N = 11 in FP32: 148 against 173), 16-bit factors at N =
+//    15 (3375 elements: 99 against 129; equal at N = 14), and FP32 from N = 8
+//    while all workgroups are resident with it (four per CU; N = 10, 1000
+//    elements: 15.0 against 16.8, 13,824: 1.06 times slower).
 // The other forms differ where the shape decides what they wait for:
 //  * whole element blocks (ax_local and the first pass of the fixed-order sum):
 //    plain stores, nothing waits for atomics, and a workgroup of few lanes only
@@ -137,8 +149,8 @@ extern "C" const char *sem_last_error(sem_ctx ctx) {
 //    122 with one; N = 5 FP64 372 with three, 395 with one (110,592 elements);
 //    N = 2 FP16 fixed order 161 with seven, 177 with four;
 //  * FP64 vectors around reduced factors: the gather outweighs the factors, and
-//    neighbours that share an L2 are worth the remap (34^3, N = 7: 148 against
-//    163; N = 8: 1.02 times slower with it);
+//    neighbours that share an L2 are worth the remap at N = 2 and 4 to 7 (34^3,
+//    N = 7: 148 against 163; N = 8: 1.02 times slower with it);
 //  * Helmholtz at N = 9: with all planes in flight two workgroups fit a CU, and
 //    while that holds the whole mesh the ring only lengthens the chain (512
 //    elements 14.5 against 15.8; 729: 25.0 against 19.8).
@@ -146,9 +158,10 @@ namespace sem {
 AxTile default_tile(int N, int64_t E, int prec, AxForm form, int num_cus) {
     AxTile t;
     t.stock = true;
-    t.xcd = 0;
-    const bool f64 = prec == SEM_FP64, f16 = !f64 && prec != SEM_FP32;
+    const bool f64 = prec == SEM_FP64, f32 = prec == SEM_FP32, f16 = !f64 && !f32;
+    const bool seven = N == 5 && f64 && E > 12 * num_cus && E <= 14 * num_cus;
     if (N == 8) t.epb = E >= 2048 ? 3 : 1;
+    else if (seven) t.epb = 7;
     else if (form == AX_BLOCKS) t.epb = N >= 6 ? 1 : N == 5 ? 3 : N == 4 ? (f16 ? 5 : 2) : N == 3 ? 4 : N == 2 ? 7 : 16;
     else if (N == 1) t.epb = 16;
     else if (N == 2) t.epb = f64 ? 8 : 4;
@@ -156,9 +169,11 @@ AxTile default_tile(int N, int64_t E, int prec, AxForm form, int num_cus) {
     else if (N == 5) t.epb = f64 ? 3 : 1;
     else if (N == 7) t.epb = f64 && E >= 32768 ? 2 : 1;
     else t.epb = 1;
-    t.pipeline = (f64 && N >= 8) || (prec == SEM_FP32 && N >= 11) ? 1 : 0;
-    if (form == AX_HELM && N == 9 && E <= 2 * num_cus) t.pipeline = 0;
-    if (form == AX_MIXED && (N == 6 || N == 7)) t.xcd = 1;
+    t.pipeline = (f64 && N >= 8) || (f32 && (N >= 11 || (N >= 8 && E <= 4 * num_cus))) || (f16 && N == 15);
+    if (form == AX_HELM && N == 9 && f64 && E <= 2 * num_cus) t.pipeline = 0;
+    const bool wide = f64 || form == AX_MIXED;      // 8-byte vectors
+    t.xcd = E <= 4096 || (form != AX_BLOCKS && wide && ((N == 1 && E >= (1 << 19)) || N == 2 || (f64 && N == 3))) ||
+            (form == AX_MIXED && N >= 4 && N <= 7);
     return t;
 }
 }  // namespace sem
@@ -315,6 +330,8 @@ extern "C" sem_status sem_bind_workspace(sem_ctx c, void *dev, size_t bytes, sem
     hipDeviceProp_t prop;
     SEM_HIP(c, hipGetDeviceProperties(&prop, dev_id));
     c->num_cus = prop.multiProcessorCount;
+    for (int p = 0; p < kNumPrec; ++p)
+        if (c->tile[p].stock) c->tile[p] = default_tile(c->N, c->E, p, AX_UNIQUE, c->num_cus);
     c->max_lds = prop.sharedMemPerBlock;
     c->ws = (char *)dev;
     c->ws_bytes = bytes;

@@ -19,9 +19,10 @@
 //   * element-interior nodes have solver indices that follow from the
 //     element index, so only element-boundary points read an index map and
 //     only they are summed (device atomics or a fixed-order second pass);
-//   * element groups go to the 8 XCDs round-robin, as the hardware deals
-//     workgroups: the factors are then read consecutively across the whole
-//     chip (contiguous ranges per XCD, a tile option, are up to 11% slower).
+//   * on large meshes element groups go to the 8 XCDs round-robin, as the
+//     hardware deals workgroups: the factors are then read consecutively across
+//     the whole chip (contiguous ranges per XCD, a tile option, are up to 11%
+//     slower there; default_tile takes them where the gather counts for more).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

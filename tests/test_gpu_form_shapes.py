@@ -71,3 +71,29 @@ def test_block_forms_fill_their_waves(K, N, prec, elements):
     print("ax_local %s N = %d, %d^3: %.1f us, %d elements per workgroup %.1f us"
           % (prec, N, K, first, elements, shared), flush=True)
     assert first <= 1.25 * shared
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K, N, prec, better", [
+    ((15, 15, 15), 5, "fp64", dict(elements_per_block=7, xcd_remap=1)),
+    ((10, 10, 10), 10, "fp32", dict(elements_per_block=1, xcd_remap=1, pipeline=1)),
+    ((9, 9, 9), 15, "fp16", dict(elements_per_block=1, xcd_remap=1, pipeline=1)),
+    ((76, 76, 76), 3, "fp64", dict(elements_per_block=2, xcd_remap=1))])
+def test_first_shape_is_not_a_slow_one(K, N, prec, better):
+    """Sizes where the shape that fits larger or smaller meshes loses 10% and
+    more: a second round of workgroups that is nearly empty, all factor planes
+    in flight with few workgroups or at the largest order, no remap at a low
+    order.  Both sides measured alike; equal shapes differ by 2%."""
+    op = _op(K, N, precisions=("fp64", prec))
+    g = torch.Generator(device="cuda").manual_seed(N)
+    u = torch.rand(op.n_unique, generator=g, dtype=torch.float64, device="cuda")
+    u = u if prec == "fp64" else u.float()
+    y = torch.zeros_like(u)
+    first = _us(lambda: op.ax(u, y, precision=prec), reps=50)
+    z = op.ax(u, precision=prec)
+    op.set_tile(prec, **{"grid_cap": 0, "pipeline": 0, **better})
+    other = _us(lambda: op.ax(u, y, precision=prec), reps=50)
+    tol = 1e-14 if prec == "fp64" else 4e-6       # copies summed in another order
+    assert float((z - op.ax(u, precision=prec)).abs().max()) <= tol * float(z.abs().max())
+    print("%s N = %d, %s: %.1f us, %s %.1f us" % (prec, N, K, first, better, other), flush=True)
+    assert first <= 1.08 * other

@@ -1199,6 +1199,7 @@ struct sem_gmres_s {
     std::vector<int32_t> first;
     double *o = nullptr;             // local solutions (FP32 ones use the first half)
     double *b0 = nullptr, *x0 = nullptr;
+    bool b0_clear = false;           // b0 is zero when queued work has run
     double *V = nullptr, *Z = nullptr, *w = nullptr, *r = nullptr;
     double *part = nullptr, *coef = nullptr;
     float *rhs32 = nullptr, *d32 = nullptr;
@@ -1614,7 +1615,9 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
     G->downer = reinterpret_cast<uint8_t *>(w + off[18]);
     G->dfmap = reinterpret_cast<int32_t *>(w + off[19]);
     G->down = reinterpret_cast<uint16_t *>(w + off[20]);
+    G->b0_clear = false;
     SEM_HIP(c, coarse_bind(G->coarse, G->cplan, w + off[23], G->b0, G->x0, s));
+    G->b0_clear = true;
     SEM_HIP(c, hipMemcpyAsync(G->dS, G->S.data(), 8 * G->S.size(), hipMemcpyHostToDevice, s));
     SEM_HIP(c, hipMemcpyAsync(G->dlam, G->lam.data(), 8 * G->lam.size(), hipMemcpyHostToDevice, s));
     G->dS32 = G->dlam32 = nullptr;
@@ -1702,6 +1705,12 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
     // half of the FP64 array)
     VT *o = reinterpret_cast<VT *>(G->o);
     constexpr bool f32 = std::is_same<VT, float>::value;
+    // The coarse solve leaves b0 cleared for the next restriction.  A call that
+    // ends with an error in between leaves it filled: cleared here then.
+    if (coarse) {
+        if (!G->b0_clear) SEM_HIP(c, launch_fill(G->b0, G->coarse->n_unique, 0.0, s));
+        G->b0_clear = false;
+    }
     if (local) {
         const VT *S, *lam;
         if constexpr (f32) {
@@ -1744,6 +1753,7 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
         // 10 Jacobi-PCG iterations from zero on the coarse operator (which
         // leave b0 cleared for the next application)
         SEM_HIP(c, coarse_solve(G->cplan, s));
+        G->b0_clear = true;
     }
     return wide_positions(G) ? combine<VT, uint64_t>(G, local ? o : nullptr, coarse, z, clear, s)
                              : combine<VT, uint32_t>(G, local ? o : nullptr, coarse, z, clear, s);

@@ -31,6 +31,7 @@
 
 #include <algorithm>
 #include <array>
+#include <cfloat>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -257,8 +258,9 @@ template <> struct GmAcc<float> {
     }
 };
 
-// 1 / x to rounding for positive normal x (the hardware estimate and two
-// Newton steps; a division adds scaling for the ends of the exponent range).
+// 1 / x to rounding for positive normal x (the hardware estimate and Newton
+// steps; a division adds scaling for the ends of the exponent range).  The FP32
+// tables are scaled so that every sum it is used on is normal.
 __device__ __forceinline__ double gm_inverse(double x) {
     double y = __builtin_amdgcn_rcp(x);
     y = fma(fma(-x, y, 1.0), y, y);
@@ -1625,8 +1627,22 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
         G->dS32 = reinterpret_cast<float *>(w + off[21]);
         G->dlam32 = reinterpret_cast<float *>(w + off[22]);
         // rounded once; the copies are synchronous (the host buffers are
-        // temporaries)
-        std::vector<float> s32(G->S.begin(), G->S.end()), l32(G->lam.begin(), G->lam.end());
+        // temporaries).  The eigenvalues are scaled by a power of two of the
+        // element's largest sum, half of which goes with S_r in either direction:
+        // sums from element lengths above 1e19 or below 1e-18 leave FP32's
+        // normal range, outside which the hardware's reciprocal estimate is 0
+        // or infinite
+        const size_t C = (size_t)G->NE * G->NE, NE = G->NE;
+        std::vector<float> s32(G->S.begin(), G->S.end()), l32(G->lam.size());
+        for (int64_t e = 0; e < c->E; ++e) {
+            const double *lam = G->lam.data() + (size_t)e * 3 * NE;
+            const double top = lam[NE - 1] + lam[2 * NE - 1] + lam[3 * NE - 1];
+            const int ex = top > 0.0 && top <= DBL_MAX ? std::ilogb(top) / 2 : 0;
+            for (size_t q = 0; q < 3 * NE; ++q)
+                l32[(size_t)e * 3 * NE + q] = (float)std::ldexp(lam[q], -2 * ex);
+            for (size_t q = 0; q < C; ++q)
+                s32[(size_t)e * 3 * C + q] = (float)std::ldexp(G->S[(size_t)e * 3 * C + q], -ex);
+        }
         SEM_HIP(c, hipMemcpyAsync(G->dS32, s32.data(), 4 * s32.size(), hipMemcpyHostToDevice, s));
         SEM_HIP(c, hipMemcpyAsync(G->dlam32, l32.data(), 4 * l32.size(), hipMemcpyHostToDevice, s));
         SEM_HIP(c, hipStreamSynchronize(s));

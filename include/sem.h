@@ -451,7 +451,7 @@ sem_status sem_proj_solve(sem_proj proj, const double *b, double *x,
  * The context must have geometry and opts.solver = 1, 2 <= N <= 13, and the
  * Poisson operator (SEM_ERR_UNSUPPORTED for a Helmholtz pair).  The solver
  * owns an internal N = 1 context (host data); device memory is one
- * caller-owned workspace (about (2 restart + 4) unique vectors; per element
+ * caller-owned workspace (about (2 restart + 2.5) unique vectors; per element
  * the eigenvectors 3 (N+3)^2, the gather map (N+3)^3 and the local solution
  * (N+1)^3 + 6 (N+1)^2; and the coarse context's workspace).  sem_gmres_bind_workspace uploads the
  * preconditioner and sets up the coarse geometry (synchronises `stream`).

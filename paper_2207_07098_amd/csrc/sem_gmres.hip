@@ -1182,6 +1182,7 @@ struct sem_gmres_s {
     std::vector<int32_t> ghost;      // [E][6][(N+1)^2]
     std::vector<int32_t> cmap;       // [E][8]
     std::vector<NbrFace> nbr;        // [E][6]
+    int64_t nfaces = 0;              // faces with a neighbour
     std::vector<uint8_t> owner;      // [E][n_b] first copy of each boundary node
     // device
     char *ws = nullptr;
@@ -1303,6 +1304,7 @@ static sem_status build_local(sem_gmres G) {
         for (int f = 0; f < 6; ++f) {
             const int64_t n = nbr[e * 6 + f];
             if (n < 0) continue;
+            G->nfaces += 1;
             // corners (0,0), (1,0), (0,1) of e's face in n's local frame
             int loc[3][3];
             const int pq[3][2] = {{0, 0}, {1, 0}, {0, 1}};
@@ -1498,22 +1500,34 @@ static size_t gm_layout(sem_gmres G, size_t *off) {
         return r;
     };
     off[0] = take(G->coarse_ws);
+    // the coarse context's partial sums, which only its own CG would use, give
+    // their place to other arrays while it lasts
+    size_t spare = G->coarse->L.partials, spare_end = spare + kPartialsBytes;
+    auto take_spare = [&](size_t b) {
+        if (spare + align256(b) > spare_end) return take(b);
+        const size_t r = spare;
+        spare += align256(b);
+        return off[0] + r;
+    };
     off[1] = take(8 * (size_t)E * 3 * NE * NE);       // S
     off[2] = take(8 * (size_t)E * 3 * NE);            // lambda
-    off[3] = take(4 * (size_t)E * 6 * n1 * n1);       // ghost map
     off[4] = take(4 * (size_t)E * 8);                 // coarse map
     off[5] = take(sizeof(NbrFace) * (size_t)E * 6);   // neighbour faces
     off[6] = take(8 * 16);                            // xi
-    off[7] = take(8 * (size_t)E * box_size(G));       // local solutions
+    // Local solutions, live from k_fdm to k_fdm_sum of one application only.
+    // Two arrays lie in the same place: the ghost map, read while the box maps
+    // are built, and r, read between a residual and the first application of
+    // the cycle that it starts.
+    off[3] = off[13] = off[7] = take(8 * (size_t)E * box_size(G));
     off[8] = take(8 * (size_t)G->coarse->n_unique);   // b0
     off[9] = take(8 * (size_t)G->coarse->n_unique);   // x0
     off[10] = take(8 * (size_t)G->ld * (G->m + 1));   // V
     off[11] = take(8 * (size_t)G->ld * G->m);         // Z
-    off[12] = take(8 * (size_t)c->n_unique);          // w
-    off[13] = take(8 * (size_t)c->n_unique);          // r
-    off[14] = take(8 * (size_t)kGmGrid * (2 * kGmMaxVec + 3));   // partial sums, at most 2 L + 3 per block
+    off[12] = take(8 * (size_t)c->n_unique);          // w, FP32 vectors in its first half
+    off[14] = take_spare(8 * (size_t)kGmGrid * (2 * kGmMaxVec + 3));   // partial sums, at most 2 L + 3 per block
     off[15] = take(8 * kGmCoef);
-    off[16] = take(4 * (size_t)c->n_unique);          // FP32 inner right-hand side
+    // the FP32 inner right-hand side, read before the cycle's first operator
+    off[16] = off[12] + 4 * (size_t)c->n_unique;
     off[17] = take(4 * (size_t)c->n_unique);          // FP32 inner correction
     off[18] = take((size_t)E * c->nb);                // owner flags
     off[19] = take(4 * (size_t)E * NE * NE * NE);    // box gather map
@@ -1522,12 +1536,12 @@ static size_t gm_layout(sem_gmres G, size_t *off) {
     const bool low = (c->precisions & ~SEM_PREC_BIT(SEM_FP64)) != 0;
     off[21] = take(low ? 4 * (size_t)E * 3 * NE * NE : 0);
     off[22] = take(low ? 4 * (size_t)E * 3 * NE : 0);
-    off[23] = take(coarse_bytes(G->cplan));
+    off[23] = take_spare(coarse_bytes(G->cplan));
     // position lists of the boundary nodes: at most every element-boundary
-    // point and the rim of every extension plane
+    // point and the rim of the extension plane over every face with a neighbour
     const size_t is = wide_positions(G) ? 8 : 4;
     off[24] = take(is * ((size_t)c->n_bnd + 1));
-    off[25] = take(is * (size_t)E * (c->nb + 6 * 4 * c->N));
+    off[25] = take(is * ((size_t)E * c->nb + (size_t)G->nfaces * 4 * c->N));
     off[26] = take(4 * (size_t)NE * NE * NE);         // storage positions of a box
     off[27] = take(4 * ((size_t)E + 1));              // first owned boundary node
     return o;
@@ -1959,7 +1973,9 @@ static sem_status residual(sem_gmres G, int prec, const T *b, const T *x, T *r, 
 // Flexible GMRES(m) cycles on A x = b in T vectors (operator precision
 // prec) until ||b - A x|| <= atol (recurrence estimate within a cycle, true
 // residual at its end) or max_iter steps in all.  V, Z, w, r live in the
-// solver's basis arrays (FP32 vectors use the first half of each slot).
+// solver's basis arrays (FP32 vectors use the first half of each slot).  b may
+// lie in the second half of w and r among the local solutions: with one_cycle
+// neither is read once the first application has started.
 // Returns SEM_OK when converged, SEM_ERR_NOT_CONVERGED at the cap; *res_out
 // is the last true residual norm.  one_cycle (inner solves of the
 // refinement): a single cycle from x = 0 that stops on the recurrence

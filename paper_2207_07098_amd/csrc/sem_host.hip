@@ -304,7 +304,7 @@ static void compute_layout(sem_ctx c) {
             L.w32 = take(4 * nu);
         }
     }
-    L.partials = take(8 * (size_t)kMaxPartials * 16);
+    L.partials = take(kPartialsBytes);
     L.state = take(sizeof(CgState) * 4);
     L.errflag = take(256);
     L.total = off;

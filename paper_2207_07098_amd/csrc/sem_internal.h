@@ -20,6 +20,7 @@ constexpr int kMaxPartials = 1 << 17;  // per-block partial sums of one reductio
 #endif
 constexpr int kVecMaxBlocks = SEM_VEC_MAX_BLOCKS;  // grid of the grid-stride vector kernels
 static_assert(kVecMaxBlocks <= kMaxPartials, "vector partials exceed the partials buffer");
+constexpr size_t kPartialsBytes = (size_t)8 * kMaxPartials * 16;   // four sites of up to four values
 constexpr int kNumPrec = 4;
 
 // Byte offsets of every array inside the caller's workspace.
@@ -150,7 +151,7 @@ inline CgState *state_ptr(sem_ctx c) {
 // once per device, and its size in bytes.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 constexpr size_t kStaticStateBytes = 4096;
-constexpr size_t kStaticPartialBytes = (size_t)8 * kMaxPartials * 16;
+constexpr size_t kStaticPartialBytes = kPartialsBytes;
 hipError_t static_scratch(void **ptr);
 
 // ---- kernel launchers (sem_kernels.hip) ----

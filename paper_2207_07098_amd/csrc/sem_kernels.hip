@@ -46,12 +46,18 @@ constexpr int kVecBlock = 512;
 // The vectors' limit is where they stop staying in the 256 MB Infinity Cache.
 // PCG per iteration at N = 7, separate launches -> fused: FP64 12^3 37.1 ->
 // 29.7 us, 16^3 64.3 -> 54.7, 24^3 (193 MB) 159.7 -> 151.6, 28^3 (305 MB) 240 ->
-// 233, but 32^3 (456 MB) 350 -> 353 and 48^3 1159 -> 1222; FP32 32^3 (228 MB) 206
-// -> 198, but 40^3 (444 MB) 369 -> 390.  16384 partials are the most that a
-// measured fused mesh had.  Grids of 512 and 2048 workgroups: 152.7 and 157.9 us
-// at 24^3 in FP64.
+// 233, but 32^3 (456 MB) 350 -> 353 and 48^3 1159 -> 1222; FP32 32^3 (228 MB) 226
+// -> 209, but 40^3 (444 MB) 369 -> 390.
+// The partials' limit is where reading them in every workgroup costs more than
+// two launches: from N = 5 on it lies above the largest cached mesh of one
+// element a workgroup (32,768 groups: FP64 N = 6 247 -> 244, FP32 N = 6 and 7 174
+// -> 160 and 226 -> 209), at lower orders, whose groups hold fewer nodes, near 24
+// thousand (17,969 groups: FP64 N = 3 and 4 77 -> 73 and 107 -> 103; 24,389 at N =
+// 2 136 either way; 32,000: 119 -> 122 and 172 -> 175; 35,937 at N = 3 in FP32 73
+// -> 76).  Grids of 512 and 2048 workgroups: 152.7 and 157.9 us at 24^3 in FP64.
 constexpr int64_t kCachedVectors = (int64_t)320 << 20;
-constexpr int kFusedPartials = 16384;
+constexpr int kFusedPartials = 24576, kFusedPartialsN5 = 32768;
+constexpr int kFusedBatchPartials = 16384;    // the most that a measured batch had
 constexpr unsigned kFusedGrid = 1024;
 
 struct bf16_t {
@@ -1580,9 +1586,9 @@ struct Vec<float> {
 };
 
 // Streaming accesses of the vector kernels (each vector is touched once per
-// kernel): with a non-temporal hint unless the solver's vectors stay in the
-// Infinity Cache from one kernel to the next (FP64 PCG at 24^3, N = 7 with the
-// hint 174.5, without 168.7 us per iteration; 32^3 356.7 and 376.9 us).
+// kernel): with a non-temporal hint except in the fused iteration, whose vectors
+// stay in the Infinity Cache from one kernel to the next (FP64 PCG at 24^3, N = 7
+// with the hint 174.5, without 168.7 us per iteration; 32^3 356.7 and 376.9 us).
 template <bool NT, typename V>
 __device__ __forceinline__ V vld(const V *p) {
     if (NT) return __builtin_nontemporal_load(p);
@@ -1633,7 +1639,7 @@ __device__ __forceinline__ void load_partials(const double *__restrict__ part, i
 // vectors of the workgroup are requested before the sum.  A k_finish launch
 // between two kernels costs 4 to 6 us and a gap, two per iteration: 4^3, N = 5
 // 20.8 -> 13.6 us per iteration, 11^3, N = 8 45.1 -> 37.8 us; larger meshes and
-// the limit at kCachedVectors.
+// both limits at kCachedVectors.
 
 // r -= alpha w and the reductions r.r, r.z (z = dinv r) for beta.  The
 // matching x += alpha p is left to k_cg_p, which reads the old p anyway, so
@@ -2443,7 +2449,9 @@ hipError_t launch_cg_iteration(sem_ctx c, int level, int prec, void *x, void *r,
     const Layout &L = c->L;
     hipError_t e;
     const bool vec64 = level == 0;     // level 0: FP64 vectors (any operator precision)
-    int fuse = 5 * c->n_unique * (vec64 ? 8 : 4) <= kCachedVectors ? kFusedPartials : 0;
+    int fuse = 5 * c->n_unique * (vec64 ? 8 : 4) > kCachedVectors ? 0
+               : c->N >= 5                                          ? kFusedPartialsN5
+                                                                    : kFusedPartials;
     if (deterministic && (prec == SEM_FP64 || !vec64)) {
         e = launch_ax(c, prec, p, w, 0, OUT_COMPACT, partials_site(c, 0), st, c->tile[prec], s, false,
                       &fuse);
@@ -2543,13 +2551,14 @@ static void launch_batch_operator(const BatchLaunch &bl, const BatchArgs &A, hip
     }
 }
 
-// Fused under the same limits as the iteration of a single mesh.
+// Fused while the vectors of all problems stay cached (as for a single mesh) and
+// no problem leaves more partials than kFusedBatchPartials.
 template <typename T>
 static hipError_t batch_iteration(const BatchLaunch &bl, hipStream_t s, int phase) {
     BatchArgs A = batch_args(bl, phase);
     const dim3 g(bl.vec_grid), t(256);
     launch_batch_operator<T>(bl, A, s);
-    if (5 * bl.n_total * (int64_t)sizeof(T) <= kCachedVectors && bl.max_partials <= kFusedPartials) {
+    if (5 * bl.n_total * (int64_t)sizeof(T) <= kCachedVectors && bl.max_partials <= kFusedBatchPartials) {
         hipLaunchKernelGGL((k_vec_batch<T, false, true>), g, t, 0, s, A);
         hipLaunchKernelGGL((k_vec_batch<T, true, true>), g, t, 0, s, A);
         return hipGetLastError();

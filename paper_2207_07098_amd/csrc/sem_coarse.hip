@@ -28,10 +28,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <thread>
 
 #include "sem_coarse.h"
 #include "sem_reduce.h"
+#include "sem_threads.h"
 
 namespace sem {
 
@@ -463,7 +463,7 @@ void coarse_pattern(sem_ctx c, CoarsePlan &plan) {
     plan.n = n;
     plan.ld = (int64_t)(a256(4 * (size_t)n) / 4);
     std::vector<std::vector<int32_t>> rows(n);
-    auto work = [&](int64_t g0, int64_t g1) {
+    host_ranges(n, [&](int64_t g0, int64_t g1) {
         for (int64_t g = g0; g < g1; ++g) {
             if (c->bdir[g]) continue;
             std::vector<int32_t> &r = rows[g];
@@ -478,11 +478,7 @@ void coarse_pattern(sem_ctx c, CoarsePlan &plan) {
             std::sort(r.begin(), r.end());
             r.erase(std::unique(r.begin(), r.end()), r.end());
         }
-    };
-    const int nth = (int)std::max<unsigned>(1, std::min<unsigned>(16, std::thread::hardware_concurrency()));
-    std::vector<std::thread> th;
-    for (int t = 0; t < nth; ++t) th.emplace_back(work, n * t / nth, n * (t + 1) / nth);
-    for (auto &t : th) t.join();
+    });
     size_t w = 1;
     for (auto &r : rows) w = std::max(w, r.size());
     plan.width = (int)((w + kCoarseUnroll - 1) / kCoarseUnroll) * kCoarseUnroll;

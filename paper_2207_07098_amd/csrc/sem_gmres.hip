@@ -36,13 +36,14 @@
 #include <cmath>
 #include <cstring>
 #include <map>
-#include <thread>
+#include <memory>
 #include <type_traits>
 #include <unordered_map>
 
 #include "sem_coarse.h"
 #include "sem_internal.h"
 #include "sem_reduce.h"
+#include "sem_threads.h"
 
 using namespace sem;
 
@@ -1354,7 +1355,7 @@ static sem_status build_local(sem_gmres G) {
         }
     G->S.assign((size_t)E * 3 * NE * NE, 0.0);
     G->lam.assign((size_t)E * 3 * NE, 0.0);
-    auto work = [&](int64_t e0, int64_t e1) {
+    host_ranges(E, [&](int64_t e0, int64_t e1) {
         std::vector<double> Kl((size_t)(3 * N + 1) * (3 * N + 1)), Ml(3 * N + 1);
         std::vector<double> A((size_t)NE * NE), Vv, lm;
         std::vector<double> Ke((size_t)NE * NE), Me(NE);
@@ -1397,26 +1398,22 @@ static sem_status build_local(sem_gmres G) {
                 double *lmb = G->lam.data() + ((size_t)e * 3 + d) * NE;
                 for (int mo = 0; mo < NE; ++mo) lmb[mo] = lm[mo];
             }
-    };
-    const int nth = (int)std::max<unsigned>(1, std::min<unsigned>(16, std::thread::hardware_concurrency()));
-    std::vector<std::thread> th;
-    for (int t = 0; t < nth; ++t)
-        th.emplace_back(work, E * t / nth, E * (t + 1) / nth);
-    for (auto &t : th) t.join();
+    });
     return SEM_OK;
 }
 
-extern "C" sem_status sem_gmres_create(sem_ctx c, int restart, sem_gmres *out) {
-    if (!c || !out) return fail(c, SEM_ERR_INVALID, "null argument");
-    *out = nullptr;
-    if (!c->geometry_ready || c->corner_xyz.empty())
-        return fail(c, SEM_ERR_STATE, "geometry not set");
-    if (!c->solver || !c->L.r64) return fail(c, SEM_ERR_STATE, "context set up without solver vectors");
-    if (c->N < 2 || c->N > 13) return fail(c, SEM_ERR_UNSUPPORTED, "the Schwarz solves need 2 <= N <= 13");
-    if (restart < 1 || restart > kGmMaxVec - 1)
-        return fail(c, SEM_ERR_INVALID, "restart must be in 1.." + std::to_string(kGmMaxVec - 1));
-    if (c->helm) return fail(c, SEM_ERR_UNSUPPORTED, "the pressure solver is for the Poisson operator");
-    sem_gmres G = new sem_gmres_s();
+// What host allocations throw does not cross the C interface: `report` makes a
+// status of its message.
+template <typename F, typename R>
+static sem_status no_throw(F call, R report) {
+    try {
+        return call();
+    } catch (const std::exception &e) {
+        return report(SEM_ERR_OOM, std::string("host memory: ") + e.what());
+    }
+}
+
+static sem_status create(sem_ctx c, int restart, sem_gmres G) {
     G->ctx = c;
     G->m = restart;
     G->NE = c->N + 3;
@@ -1432,22 +1429,13 @@ extern "C" sem_status sem_gmres_create(sem_ctx c, int restart, sem_gmres *out) {
     sem_status st = sem_setup(&m0, 1, &o0, &G->coarse);
     if (st) {
         const std::string msg = std::string("coarse grid: ") + sem_last_error(nullptr);
-        delete G;
         return fail(c, st, msg);
     }
     st = sem_workspace_size(G->coarse, &G->coarse_ws);
-    if (st) {
-        sem_free(G->coarse);
-        delete G;
-        return fail(c, st, "coarse grid workspace");
-    }
+    if (st) return fail(c, st, "coarse grid workspace");
     coarse_pattern(G->coarse, G->cplan);
     st = build_local(G);
-    if (st) {
-        sem_free(G->coarse);
-        delete G;
-        return st;
-    }
+    if (st) return st;
     // the first copy of every element-boundary node owns it
     G->owner.assign((size_t)c->E * c->nb, 0);
     // (boundary nodes are numbered by first appearance, so an element owns a
@@ -1467,8 +1455,29 @@ extern "C" sem_status sem_gmres_create(sem_ctx c, int restart, sem_gmres *out) {
             const int32_t v = G->coarse->bmap[(size_t)e * G->coarse->nb + q];
             G->cmap[e * 8 + q] = v < 0 ? -1 : v;
         }
-    *out = G;
     return SEM_OK;
+}
+
+extern "C" sem_status sem_gmres_create(sem_ctx c, int restart, sem_gmres *out) {
+    if (!c || !out) return fail(c, SEM_ERR_INVALID, "null argument");
+    *out = nullptr;
+    if (!c->geometry_ready || c->corner_xyz.empty())
+        return fail(c, SEM_ERR_STATE, "geometry not set");
+    if (!c->solver || !c->L.r64) return fail(c, SEM_ERR_STATE, "context set up without solver vectors");
+    if (c->N < 2 || c->N > 13) return fail(c, SEM_ERR_UNSUPPORTED, "the Schwarz solves need 2 <= N <= 13");
+    if (restart < 1 || restart > kGmMaxVec - 1)
+        return fail(c, SEM_ERR_INVALID, "restart must be in 1.." + std::to_string(kGmMaxVec - 1));
+    if (c->helm) return fail(c, SEM_ERR_UNSUPPORTED, "the pressure solver is for the Poisson operator");
+    struct Free {
+        void operator()(sem_gmres g) const { sem_gmres_free(g); }
+    };
+    auto build = [&]() -> sem_status {
+        std::unique_ptr<sem_gmres_s, Free> g(new sem_gmres_s());
+        const sem_status st = create(c, restart, g.get());
+        if (!st) *out = g.release();
+        return st;
+    };
+    return no_throw(build, [&](sem_status st, const std::string &m) { return fail(c, st, m); });
 }
 
 extern "C" void sem_gmres_free(sem_gmres G) {
@@ -1583,9 +1592,7 @@ static hipError_t build_positions(sem_gmres G, hipStream_t s) {
     return e == hipSuccess ? hipStreamSynchronize(s) : e;   // hoff is a temporary
 }
 
-extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t bytes,
-                                               sem_stream stream) {
-    if (!G || !dev) return gfail(G, SEM_ERR_INVALID, "null argument");
+static sem_status bind_workspace(sem_gmres G, void *dev, size_t bytes, sem_stream stream) {
     size_t off[28];
     const size_t need = gm_layout(G, off);
     if (bytes < need)
@@ -1695,6 +1702,13 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
     SEM_HIP(c, pe);
     SEM_HIP(c, hipStreamSynchronize(s));
     return SEM_OK;
+}
+
+extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t bytes,
+                                               sem_stream stream) {
+    if (!G || !dev) return gfail(G, SEM_ERR_INVALID, "null argument");
+    return no_throw([&]() { return bind_workspace(G, dev, bytes, stream); },
+                    [&](sem_status st, const std::string &m) { return gfail(G, st, m); });
 }
 
 // z from the local solutions (o null: without them) and the coarse solution.

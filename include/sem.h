@@ -449,7 +449,8 @@ sem_status sem_proj_solve(sem_proj proj, const double *b, double *x,
  *                  projection of each new basis vector made during the next
  *                  step (two sweeps over the basis per step), FP64 sums.
  * The context must have geometry and opts.solver = 1, 2 <= N <= 13, and the
- * Poisson operator (SEM_ERR_UNSUPPORTED for a Helmholtz pair).  The solver
+ * Poisson operator (SEM_ERR_UNSUPPORTED for a Helmholtz pair, and for more than
+ * 2^32 values of the local solutions, about 280 GB).  The solver
  * owns an internal N = 1 context (host data); device memory is one
  * caller-owned workspace (about (2 restart + 2.5) unique vectors; per element
  * the eigenvectors 3 (N+3)^2, the gather map (N+3)^3 and the local solution

@@ -132,11 +132,11 @@ struct FdmParams {
 // (solver order of the element interior), of its boundary points (order of the
 // element map), then of the six extension planes (p + n1 q each), so that the
 // sum reads contiguous runs; edges and corners of the extension carry no data.
-// Padded to whole 128-byte lines of FP64.
+// Padded to multiples of 64 bytes of FP64.
 template <int NE>
 struct BoxStore {
     static constexpr int N = NE - 3, N1 = N + 1, NI = (N - 1) * (N - 1) * (N - 1),
-                         NB = N1 * N1 * N1 - NI, F2 = N1 * N1, SIZE = (NI + NB + 6 * F2 + 15) / 16 * 16;
+                         NB = N1 * N1 * N1 - NI, F2 = N1 * N1, SIZE = (NI + NB + 6 * F2 + 7) / 8 * 8;
     // position of box point (a, b, c), -1 for the edges and corners
     static __device__ int at(int a, int b, int c) {
         const int i = a - 1, j = b - 1, k = c - 1;
@@ -573,13 +573,14 @@ __global__ void __launch_bounds__(64) k_restrict_e(CoarseParams<VT> P) {
 //     solver order): a list of storage positions built at bind time (k_sum_count,
 //     k_sum_fill, k_sum_sort), the element's own copy in front, which also
 //     places the node for P.
-// I: 32-bit positions while they fit, 64-bit ones above.
+// Positions have 32 bits: the smallest mesh with more (48.8 million elements at
+// N = 2) needs 315 GB of workspaces, beyond the card's memory.
 struct NbrFace {
     int32_t e;                // neighbour across the face or -1
     int32_t base, sp, sq;     // its storage position of face point (p, q): base + p sp + q sq
 };
 
-template <typename VT, typename I>
+template <typename VT>
 struct SumParams {
     const VT *o;              // [E][BoxStore::SIZE] local solutions, or null (no local part)
     VT *z;
@@ -589,14 +590,14 @@ struct SumParams {
     const int32_t *cmap;      // [E][8] coarse index of each element corner or -1
     const double *xi;         // GLL nodes [N+1]
     const NbrFace *nbr;       // [E][6]
-    const I *off, *pos;       // lists of the boundary nodes
+    const uint32_t *off, *pos;  // lists of the boundary nodes
     const int32_t *bpos2l;    // local index of an element's boundary point
     const int32_t *first;     // [E + 1] first boundary node that an element owns
     int64_t E, n_bnd;
 };
 
-template <int NE, typename VT, typename I>
-__global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT, I> P) {
+template <int NE, typename VT>
+__global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT> P) {
     using St = BoxStore<NE>;
     constexpr int N = St::N, N1 = St::N1, NM = N - 1, NI = St::NI, NF = NM * NM;
     constexpr int QI = (NI + 63) / 64, QF = (NF + 63) / 64, W = kGmBlock / 64;
@@ -668,8 +669,8 @@ __global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT, I> P) {
     // lists requested together (a pass waits for off, pos and the values in turn)
     constexpr int U = 2, V = 4;
     for (int32_t ga = g0 + lane; ga < g1; ga += 64 * U) {
-        I lo[U], hi[U], own[U];
-        I at[U][V];
+        uint32_t lo[U], hi[U], own[U];
+        uint32_t at[U][V];
         double sum[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -681,7 +682,7 @@ __global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT, I> P) {
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int t = 0; t < V; ++t)
-                at[u][t] = lo[u] < hi[u] ? P.pos[lo[u] + t < hi[u] ? lo[u] + t : lo[u]] : (I)0;
+                at[u][t] = lo[u] < hi[u] ? P.pos[lo[u] + t < hi[u] ? lo[u] + t : lo[u]] : 0u;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             own[u] = at[u][0];
@@ -701,11 +702,11 @@ __global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT, I> P) {
             double z = 0.0;
             if (lo[u] < hi[u]) {                      // else a Dirichlet node: 0
                 if (P.o) {
-                    for (I t = lo[u] + V; t < hi[u]; ++t) sum[u] += (double)P.o[P.pos[t]];
+                    for (uint32_t t = lo[u] + V; t < hi[u]; ++t) sum[u] += (double)P.o[P.pos[t]];
                     z = sum[u] * (1.0 / (double)(hi[u] - lo[u]));
                 }
                 if (P.x0) {
-                    const int l = b2l[(int)(own[u] - (I)e * (I)B) - NI];
+                    const int l = b2l[(int)(own[u] - (uint32_t)(e * B)) - NI];
                     z += coarse(l % N1, l / N1 % N1, l / St::F2);
                 }
             }
@@ -733,7 +734,6 @@ __global__ void __launch_bounds__(kGmBlock) k_fdm_sum(SumParams<VT, I> P) {
 // Lists of the storage positions of every boundary node: counts, then
 // positions (in any order), then each list in ascending order with its first
 // element point in front.  `cur` starts at zero for both.
-template <int NE>
 __global__ void __launch_bounds__(kGmBlock) k_sum_count(int64_t npoints, int64_t n_bnd,
                                                         const int32_t *__restrict__ fmap,
                                                         uint32_t *__restrict__ cur) {
@@ -744,38 +744,38 @@ __global__ void __launch_bounds__(kGmBlock) k_sum_count(int64_t npoints, int64_t
     }
 }
 
-template <int NE, typename I>
+template <int NE>
 __global__ void __launch_bounds__(kGmBlock) k_sum_fill(int64_t npoints, int64_t n_bnd,
                                                        const int32_t *__restrict__ fmap,
                                                        const int32_t *__restrict__ at,
-                                                       const I *__restrict__ off,
+                                                       const uint32_t *__restrict__ off,
                                                        uint32_t *__restrict__ cur,
-                                                       I *__restrict__ pos) {
+                                                       uint32_t *__restrict__ pos) {
     constexpr int B = NE * NE * NE;
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < npoints;
          x += (int64_t)gridDim.x * blockDim.x) {
         const int32_t g = fmap[x];
         if (g >= 0 && g < n_bnd)
-            pos[off[g] + atomicAdd(cur + g, 1u)] = (I)(x / B) * (I)BoxStore<NE>::SIZE + (I)at[x % B];
+            pos[off[g] + atomicAdd(cur + g, 1u)] = (uint32_t)(x / B) * BoxStore<NE>::SIZE + at[x % B];
     }
 }
 
-template <int NE, typename I>
-__global__ void __launch_bounds__(kGmBlock) k_sum_sort(int64_t n_bnd, const I *__restrict__ off,
-                                                       I *__restrict__ pos) {
+template <int NE>
+__global__ void __launch_bounds__(kGmBlock) k_sum_sort(int64_t n_bnd, const uint32_t *__restrict__ off,
+                                                       uint32_t *__restrict__ pos) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= n_bnd) return;
-    const I lo = off[g], hi = off[g + 1];
-    for (I t = lo + 1; t < hi; ++t) {
-        const I x = pos[t];
-        I u = t;
+    const uint32_t lo = off[g], hi = off[g + 1];
+    for (uint32_t t = lo + 1; t < hi; ++t) {
+        const uint32_t x = pos[t];
+        uint32_t u = t;
         for (; u > lo && pos[u - 1] > x; --u) pos[u] = pos[u - 1];
         pos[u] = x;
     }
-    for (I t = lo; t < hi; ++t) {
-        const I x = pos[t];
-        if ((int)(x % (I)BoxStore<NE>::SIZE) < BoxStore<NE>::NI + BoxStore<NE>::NB) {
-            for (I u = t; u > lo; --u) pos[u] = pos[u - 1];
+    for (uint32_t t = lo; t < hi; ++t) {
+        const uint32_t x = pos[t];
+        if ((int)(x % (uint32_t)BoxStore<NE>::SIZE) < BoxStore<NE>::NI + BoxStore<NE>::NB) {
+            for (uint32_t u = t; u > lo; --u) pos[u] = pos[u - 1];
             pos[lo] = x;
             break;
         }
@@ -1197,7 +1197,7 @@ struct sem_gmres_s {
     int32_t *dfmap = nullptr;
     uint16_t *down = nullptr;
     NbrFace *dnbr = nullptr;
-    void *doff = nullptr, *dpos = nullptr;   // storage positions of the boundary nodes
+    uint32_t *doff = nullptr, *dpos = nullptr;   // storage positions of the boundary nodes
     int32_t *dat = nullptr;          // storage positions of a box
     int32_t *dfirst = nullptr;       // [E + 1] first boundary node that an element owns
     std::vector<int32_t> first;
@@ -1402,6 +1402,9 @@ static sem_status build_local(sem_gmres G) {
     return SEM_OK;
 }
 
+// BoxStore::SIZE at run time.
+static int64_t box_size(int n1) { return (n1 * n1 * n1 + 6 * n1 * n1 + 7) / 8 * 8; }
+
 // What host allocations throw does not cross the C interface: `report` makes a
 // status of its message.
 template <typename F, typename R>
@@ -1468,6 +1471,8 @@ extern "C" sem_status sem_gmres_create(sem_ctx c, int restart, sem_gmres *out) {
     if (restart < 1 || restart > kGmMaxVec - 1)
         return fail(c, SEM_ERR_INVALID, "restart must be in 1.." + std::to_string(kGmMaxVec - 1));
     if (c->helm) return fail(c, SEM_ERR_UNSUPPORTED, "the pressure solver is for the Poisson operator");
+    if (c->E > (int64_t)UINT32_MAX / box_size(c->n1))
+        return fail(c, SEM_ERR_UNSUPPORTED, "more local-solve values than 32 bits count");
     struct Free {
         void operator()(sem_gmres g) const { sem_gmres_free(g); }
     };
@@ -1489,15 +1494,6 @@ extern "C" void sem_gmres_free(sem_gmres G) {
 }
 
 extern "C" const char *sem_gmres_last_error(sem_gmres G) { return G ? G->err.c_str() : ""; }
-
-// BoxStore::SIZE at run time, and whether its positions exceed 32 bits.
-static int64_t box_size(sem_gmres G) {
-    const int n1 = G->ctx->n1;
-    return (n1 * n1 * n1 + 6 * n1 * n1 + 15) / 16 * 16;
-}
-static bool wide_positions(sem_gmres G) {
-    return (uint64_t)G->ctx->E * box_size(G) > UINT32_MAX;
-}
 
 static size_t gm_layout(sem_gmres G, size_t *off) {
     sem_ctx c = G->ctx;
@@ -1527,7 +1523,7 @@ static size_t gm_layout(sem_gmres G, size_t *off) {
     // Two arrays lie in the same place: the ghost map, read while the box maps
     // are built, and r, read between a residual and the first application of
     // the cycle that it starts.
-    off[3] = off[13] = off[7] = take(8 * (size_t)E * box_size(G));
+    off[3] = off[13] = off[7] = take(8 * (size_t)E * box_size(n1));
     off[8] = take(8 * (size_t)G->coarse->n_unique);   // b0
     off[9] = take(8 * (size_t)G->coarse->n_unique);   // x0
     off[10] = take(8 * (size_t)G->ld * (G->m + 1));   // V
@@ -1548,9 +1544,8 @@ static size_t gm_layout(sem_gmres G, size_t *off) {
     off[23] = take_spare(coarse_bytes(G->cplan));
     // position lists of the boundary nodes: at most every element-boundary
     // point and the rim of the extension plane over every face with a neighbour
-    const size_t is = wide_positions(G) ? 8 : 4;
-    off[24] = take(is * ((size_t)c->n_bnd + 1));
-    off[25] = take(is * ((size_t)E * c->nb + (size_t)G->nfaces * 4 * c->N));
+    off[24] = take(4 * ((size_t)c->n_bnd + 1));
+    off[25] = take(4 * ((size_t)E * c->nb + (size_t)G->nfaces * 4 * c->N));
     off[26] = take(4 * (size_t)NE * NE * NE);         // storage positions of a box
     off[27] = take(4 * ((size_t)E + 1));              // first owned boundary node
     return o;
@@ -1565,29 +1560,28 @@ extern "C" sem_status sem_gmres_workspace_size(sem_gmres G, size_t *bytes) {
 
 // Position lists of the boundary nodes from the box gather maps (the counts
 // are summed on the host; the local solutions' array holds them meanwhile).
-template <int NE, typename I>
+template <int NE>
 static hipError_t build_positions(sem_gmres G, hipStream_t s) {
     sem_ctx c = G->ctx;
     const int64_t nb = c->n_bnd, np = c->E * NE * NE * NE;
     uint32_t *cur = reinterpret_cast<uint32_t *>(G->o);
-    I *off = static_cast<I *>(G->doff), *pos = static_cast<I *>(G->dpos);
+    uint32_t *off = G->doff, *pos = G->dpos;
     const dim3 gp(gm_grid(np)), gn((unsigned)((nb + kGmBlock - 1) / kGmBlock)), t(kGmBlock);
-    std::vector<uint32_t> cnt(nb);
-    std::vector<I> hoff(nb + 1);
+    std::vector<uint32_t> cnt(nb), hoff(nb + 1);
     hipError_t e = launch_fill32(reinterpret_cast<float *>(cur), nb, 0.0f, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sum_count<NE>, gp, t, 0, s, np, nb, (const int32_t *)G->dfmap, cur);
+    hipLaunchKernelGGL(k_sum_count, gp, t, 0, s, np, nb, (const int32_t *)G->dfmap, cur);
     e = hipMemcpyAsync(cnt.data(), cur, 4 * (size_t)nb, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
     hoff[0] = 0;
     for (int64_t g = 0; g < nb; ++g) hoff[g + 1] = hoff[g] + cnt[g];
-    e = hipMemcpyAsync(off, hoff.data(), sizeof(I) * hoff.size(), hipMemcpyHostToDevice, s);
+    e = hipMemcpyAsync(off, hoff.data(), 4 * hoff.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = launch_fill32(reinterpret_cast<float *>(cur), nb, 0.0f, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_sum_fill<NE, I>), gp, t, 0, s, np, nb, (const int32_t *)G->dfmap,
-                       (const int32_t *)G->dat, (const I *)off, cur, pos);
-    hipLaunchKernelGGL((k_sum_sort<NE, I>), gn, t, 0, s, nb, (const I *)off, pos);
+    hipLaunchKernelGGL(k_sum_fill<NE>, gp, t, 0, s, np, nb, (const int32_t *)G->dfmap,
+                       (const int32_t *)G->dat, (const uint32_t *)off, cur, pos);
+    hipLaunchKernelGGL(k_sum_sort<NE>, gn, t, 0, s, nb, (const uint32_t *)off, pos);
     e = hipGetLastError();
     return e == hipSuccess ? hipStreamSynchronize(s) : e;   // hoff is a temporary
 }
@@ -1620,8 +1614,8 @@ static sem_status bind_workspace(sem_gmres G, void *dev, size_t bytes, sem_strea
     G->dnbr = reinterpret_cast<NbrFace *>(w + off[5]);
     G->dxi = reinterpret_cast<double *>(w + off[6]);
     G->o = reinterpret_cast<double *>(w + off[7]);
-    G->doff = w + off[24];
-    G->dpos = w + off[25];
+    G->doff = reinterpret_cast<uint32_t *>(w + off[24]);
+    G->dpos = reinterpret_cast<uint32_t *>(w + off[25]);
     G->dat = reinterpret_cast<int32_t *>(w + off[26]);
     G->dfirst = reinterpret_cast<int32_t *>(w + off[27]);
     SEM_HIP(c, hipMemcpyAsync(G->dfirst, G->first.data(), 4 * G->first.size(), hipMemcpyHostToDevice, s));
@@ -1654,16 +1648,18 @@ static sem_status bind_workspace(sem_gmres G, void *dev, size_t bytes, sem_strea
         // normal range, outside which the hardware's reciprocal estimate is 0
         // or infinite
         const size_t C = (size_t)G->NE * G->NE, NE = G->NE;
-        std::vector<float> s32(G->S.begin(), G->S.end()), l32(G->lam.size());
-        for (int64_t e = 0; e < c->E; ++e) {
-            const double *lam = G->lam.data() + (size_t)e * 3 * NE;
-            const double top = lam[NE - 1] + lam[2 * NE - 1] + lam[3 * NE - 1];
-            const int ex = top > 0.0 && top <= DBL_MAX ? std::ilogb(top) / 2 : 0;
-            for (size_t q = 0; q < 3 * NE; ++q)
-                l32[(size_t)e * 3 * NE + q] = (float)std::ldexp(lam[q], -2 * ex);
-            for (size_t q = 0; q < C; ++q)
-                s32[(size_t)e * 3 * C + q] = (float)std::ldexp(G->S[(size_t)e * 3 * C + q], -ex);
-        }
+        std::vector<float> s32(G->S.size()), l32(G->lam.size());
+        host_ranges(c->E, [&](int64_t e0, int64_t e1) {
+            for (int64_t e = e0; e < e1; ++e) {
+                const double *lam = G->lam.data() + (size_t)e * 3 * NE, *S = G->S.data() + (size_t)e * 3 * C;
+                const double top = lam[NE - 1] + lam[2 * NE - 1] + lam[3 * NE - 1];
+                const int ex = top > 0.0 && top <= DBL_MAX ? std::ilogb(top) / 2 : 0;
+                const double fl = std::ldexp(1.0, -2 * ex), fs = std::ldexp(1.0, -ex);
+                for (size_t q = 0; q < 3 * NE; ++q) l32[(size_t)e * 3 * NE + q] = (float)(lam[q] * fl);
+                for (size_t q = 0; q < 3 * C; ++q)
+                    s32[(size_t)e * 3 * C + q] = (float)(q < C ? S[q] * fs : S[q]);
+            }
+        });
         SEM_HIP(c, hipMemcpyAsync(G->dS32, s32.data(), 4 * s32.size(), hipMemcpyHostToDevice, s));
         SEM_HIP(c, hipMemcpyAsync(G->dlam32, l32.data(), 4 * l32.size(), hipMemcpyHostToDevice, s));
         SEM_HIP(c, hipStreamSynchronize(s));
@@ -1690,9 +1686,7 @@ static sem_status bind_workspace(sem_gmres G, void *dev, size_t bytes, sem_strea
     SEM_HIP(c, hipGetLastError());
     hipError_t pe = hipErrorInvalidValue;
 #define SEM_POS(ne)                                                                              \
-    case ne: pe = wide_positions(G) ? build_positions<ne, uint64_t>(G, s)                        \
-                                    : build_positions<ne, uint32_t>(G, s);                       \
-        break;
+    case ne: pe = build_positions<ne>(G, s); break;
     switch (G->NE) {
         SEM_POS(5) SEM_POS(6) SEM_POS(7) SEM_POS(8) SEM_POS(9) SEM_POS(10) SEM_POS(11) SEM_POS(12)
         SEM_POS(13) SEM_POS(14) SEM_POS(15) SEM_POS(16)
@@ -1712,16 +1706,16 @@ extern "C" sem_status sem_gmres_bind_workspace(sem_gmres G, void *dev, size_t by
 }
 
 // z from the local solutions (o null: without them) and the coarse solution.
-template <typename VT, typename I>
+template <typename VT>
 static sem_status combine(sem_gmres G, const VT *o, bool coarse, VT *z, VT *clear, hipStream_t s) {
     sem_ctx c = G->ctx;
-    SumParams<VT, I> P{o, z, clear, coarse ? G->x0 : nullptr, G->dcmap, G->dxi, G->dnbr,
-                       static_cast<const I *>(G->doff), static_cast<const I *>(G->dpos),
+    SumParams<VT> P{o, z, clear, coarse ? G->x0 : nullptr, G->dcmap, G->dxi, G->dnbr,
+                       G->doff, G->dpos,
                        dptr<int32_t>(c, c->L.bpos2l), G->dfirst, c->E, c->n_bnd};
     const dim3 g((unsigned)((c->E + kGmBlock / 64 - 1) / (kGmBlock / 64))), t(kGmBlock);
 #define SEM_SUM(ne)                                                       \
     case ne:                                                              \
-        hipLaunchKernelGGL((k_fdm_sum<ne, VT, I>), g, t, 0, s, P);        \
+        hipLaunchKernelGGL((k_fdm_sum<ne, VT>), g, t, 0, s, P);        \
         break;
     switch (G->NE) {
         SEM_SUM(5) SEM_SUM(6) SEM_SUM(7) SEM_SUM(8) SEM_SUM(9) SEM_SUM(10) SEM_SUM(11) SEM_SUM(12)
@@ -1799,8 +1793,7 @@ static sem_status precondition(sem_gmres G, const VT *r, VT *z, unsigned parts, 
         SEM_HIP(c, coarse_solve(G->cplan, s));
         G->b0_clear = true;
     }
-    return wide_positions(G) ? combine<VT, uint64_t>(G, local ? o : nullptr, coarse, z, clear, s)
-                             : combine<VT, uint32_t>(G, local ? o : nullptr, coarse, z, clear, s);
+    return combine<VT>(G, local ? o : nullptr, coarse, z, clear, s);
 }
 
 extern "C" sem_status sem_gmres_precondition(sem_gmres G, const double *r, double *z,

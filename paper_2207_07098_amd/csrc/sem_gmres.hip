@@ -226,9 +226,10 @@ template <int NE, typename VT>
 struct FdmShape {
     static constexpr int C = NE * NE, T = (C + 15) / 16, KS = (NE + 3) / 4;
     // Row pitch of the LDS buffer where a line's results go to row hi ([hi][lo
-    // + NE row]) and to row lo ([lo][row + NE hi]): the values for NE = 5..16
-    // that cost the fewest LDS cycles over the writes and reads of a pass with
-    // 16 (FP64) or 32 (FP32) lanes served per cycle (NE = 10 in FP64: 168 and
+    // + NE row]) and to row lo ([lo][row + NE hi]): for NE = 5..16 the smallest
+    // values that cost the fewest LDS cycles over the writes and reads of a pass
+    // with 16 (FP64) or 32 (FP32) lanes served per cycle, found by a search over
+    // 34 pitches (tests/test_lds_pitches.py repeats it; NE = 10 in FP64: 168 and
     // 168 cycles, none lost to conflicts; a pitch of 112 for both: 198 and 563,
     // and 62% of the LDS cycles counted as conflicts).
     static constexpr int kHi64[12] = {37, 38, 55, 72, 89, 106, 123, 156, 173, 206, 239, 256};

@@ -470,9 +470,9 @@ enum { MODE_ATOMIC = 0, MODE_COMPACT = 1, MODE_LOCAL = 2 };
 // before the gather, so the wave sees two memory round trips instead of
 // three.  It pays for 32- and 16-bit factors, whose launches are bound by
 // that chain (48^3, N = 7: FP32 0.335 -> 0.328 ms, FP16 0.318 -> 0.302 ms;
-// 24^3: 0.0545 -> 0.0518 and 0.0561 -> 0.0526 ms).  FP64 launches are bound
-// by HBM, and factors ahead of the gather only delay it (24^3: 0.086 -> 0.091
-// ms).  In the loop over groups the gather goes first as well: there the map
+// 24^3: 0.0545 -> 0.0518 and 0.0561 -> 0.0526 ms).  FP64 launches of 24^3
+// and more are bound by HBM, and factors ahead of the gather only delay it
+// (24^3: 0.086 -> 0.091 ms); smaller FP64 meshes were not timed with it.  In the loop over groups the gather goes first as well: there the map
 // comes from the previous element, and factor registers that live across
 // elements spill.
 template <int N1, int PF>

@@ -266,8 +266,8 @@ typedef struct {
 
 /* The shape that sem_ax uses on unique vectors.  Until a shape is set or
  * tuned, the other forms (E-vectors, fixed-order sums, FP64 vectors around
- * reduced factors, Helmholtz) start with shapes of their own; a shape that
- * sem_set_tile or sem_autotune leaves applies to all of them. */
+ * reduced factors, Helmholtz) start with shapes of their own; another shape
+ * that sem_set_tile or sem_autotune leaves applies to all of them. */
 sem_status sem_get_tile(sem_ctx ctx, sem_precision prec, sem_tile *tile);
 sem_status sem_set_tile(sem_ctx ctx, sem_precision prec, const sem_tile *tile);
 

@@ -648,17 +648,21 @@ static bool tile_valid(sem_ctx c, int prec, const sem_tile &t) {
     return lds <= c->max_lds;
 }
 
+// The shape a caller chose, for every form of the operator; the one that the
+// context has already (as sem_get_tile returned it) changes nothing.
+static void set_shape(AxTile &o, const sem_tile &t) {
+    o.stock = o.stock && o.epb == t.elements_per_block && o.grid_cap == t.grid_cap &&
+              o.xcd == t.xcd_remap && o.pipeline == t.pipeline;
+    o.epb = t.elements_per_block;
+    o.grid_cap = t.grid_cap;
+    o.xcd = t.xcd_remap;
+    o.pipeline = t.pipeline;
+}
+
 extern "C" sem_status sem_set_tile(sem_ctx c, sem_precision prec, const sem_tile *t) {
     if (!c || !t || (int)prec < 0 || (int)prec >= kNumPrec) return fail(c, SEM_ERR_INVALID, "bad argument");
     if (!tile_valid(c, prec, *t)) return fail(c, SEM_ERR_INVALID, "tile does not fit this order");
-    AxTile &o = c->tile[prec];
-    // what sem_get_tile returned, set again, changes nothing
-    o.stock = o.stock && o.epb == t->elements_per_block && o.grid_cap == t->grid_cap &&
-              o.xcd == t->xcd_remap && o.pipeline == t->pipeline;
-    o.epb = t->elements_per_block;
-    o.grid_cap = t->grid_cap;
-    o.xcd = t->xcd_remap;
-    o.pipeline = t->pipeline;
+    set_shape(c->tile[prec], *t);
     for (auto &g : c->graphs) (void)hipGraphExecDestroy(g.exec);
     c->graphs.clear();
     return SEM_OK;
@@ -794,7 +798,7 @@ extern "C" sem_status sem_autotune(sem_ctx c, sem_precision prec, int reps, cons
             }
     for (auto &e : ev) (void)hipEventDestroy(e);
     if (n_results) *n_results = std::min(nres, max_results);
-    c->tile[prec] = best_t;
+    set_shape(c->tile[prec], sem_tile{best_t.epb, best_t.grid_cap, best_t.xcd, best_t.pipeline});
     for (auto &g : c->graphs) (void)hipGraphExecDestroy(g.exec);
     c->graphs.clear();
     if (best) *best = sem_tile{best_t.epb, best_t.grid_cap, best_t.xcd, best_t.pipeline};
